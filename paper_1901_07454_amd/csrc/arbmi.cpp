@@ -431,6 +431,8 @@ int Sim::advance(int64_t n, const RecordArgs* rec) {
 
 StateShape Sim::state_shape() const {
     StateShape sh;
+    if (cfg.coef_mode == 3 && !timed && p.block_threads == 0 && p.cells_per_pack == 0 && cfg.block_threads != 256)
+        sh.magic = kStateMagic ^ (uint64_t(cfg.block_threads) << 56);
     sh.K = K;
     sh.bk_cap = bk_cap;
     sh.sp_cap = sp_cap;
@@ -624,7 +626,7 @@ int build_sim(const ModelView& m, const arb_params& pp, const DeviceLimits& d, S
     s->device = d.dev;
     s->n_cu = d.n_cu;
     s->lds_max = d.lds_max;
-    const Plan plan = choose_plan(m.cells, m.n_cells, m.br, m.n_br, *p, d.lds_max, d.n_cu);
+    const Plan plan = choose_plan(m.cells, m.n_cells, m.br, m.n_br, m.syn, m.n_syn, *p, d.lds_max, d.n_cu);
     LowerOptions opt;
     opt.block_threads = plan.block_threads;
     opt.coef_mode = plan.coef_mode;
@@ -651,7 +653,7 @@ int build_sim(const ModelView& m, const arb_params& pp, const DeviceLimits& d, S
             pt.block_threads = T;
             pt.coef_mode = 3;
             pt.cells_per_pack = 1;
-            const Plan pl = choose_plan(m.cells, m.n_cells, m.br, m.n_br, pt, d.lds_max, d.n_cu);
+            const Plan pl = choose_plan(m.cells, m.n_cells, m.br, m.n_br, m.syn, m.n_syn, pt, d.lds_max, d.n_cu);
             opt.block_threads = T;
             opt.reg_slots = pl.reg_slots;
             opt.reg_len = pl.reg_len;
@@ -991,7 +993,7 @@ int arb_plan_layout(const arb_cell* cells, int32_t n_cells, const arb_branch* br
     if (p->coef_mode < 0 || p->coef_mode > 3) return fail(ARB_EINVAL, "coef_mode must be 0, 1, 2 or 3");
     if (p->cells_per_pack < 0) return fail(ARB_EINVAL, "cells_per_pack must be >= 0");
     DeviceLimits d;  // MI355X: 256 CUs, 160 KiB LDS
-    const Plan plan = choose_plan(cells, n_cells, branches, n_branches, *p, d.lds_max, d.n_cu);
+    const Plan plan = choose_plan(cells, n_cells, branches, n_branches, syn, n_syn, *p, d.lds_max, d.n_cu);
     LowerOptions opt;
     opt.block_threads = plan.block_threads;
     opt.coef_mode = plan.coef_mode;
@@ -1254,7 +1256,7 @@ int arb_get_state(arb_sim s_, void* blob, int64_t cap, int64_t* n_out) {
     if (!blob) return ARB_OK;
     if (cap < total) return fail(ARB_EOVERFLOW, "state blob capacity too small");
     const int64_t np = int64_t(L.packs.size());
-    StateHeader h{kStateMagic, s->step, L.n_slots, int64_t(L.hh_cv.size()), int64_t(L.syn_global.size()),
+    StateHeader h{sh.magic, s->step, L.n_slots, int64_t(L.hh_cv.size()), int64_t(L.syn_global.size()),
                   np, np, s->bk_cap, s->sp_cap, s->sp_user};
     char* out = static_cast<char*>(blob);
     std::memcpy(out, &h, sizeof h);

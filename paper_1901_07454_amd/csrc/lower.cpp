@@ -1114,7 +1114,7 @@ std::string check_state_blob(const Lowered& L, const StateShape& sh, const void*
     std::memcpy(&h, blob, sizeof h);
     const int64_t np = int64_t(L.packs.size());
     const int64_t nhh = int64_t(L.hh_cv.size()), nsyn = int64_t(L.syn_global.size());
-    if (h.magic != kStateMagic || h.n_slots != L.n_slots || h.n_hh != nhh || h.n_syn != nsyn || h.n_packs != np ||
+    if (h.magic != sh.magic || h.n_slots != L.n_slots || h.n_hh != nhh || h.n_syn != nsyn || h.n_packs != np ||
         h.n_bk != np || h.bk_cap != sh.bk_cap || h.sp_cap != int64_t(sh.sp_cap))
         return "state blob does not belong to this model";
     int64_t bytes[kStateParts];

@@ -132,7 +132,12 @@ std::string verify_layout(const Lowered& lw);
 // external-event cursors, the running epoch's network events (offsets,
 // next-step table, synapses, weights), counters, spike buffer (gid, step,
 // time), spike history (counts, gids, steps), generated mechanisms' states.
+constexpr uint64_t kStateMagic = 0x41524233535441ull;
 struct StateShape {
+    // kStateMagic, or a value of its own where the library chose a workgroup
+    // of other than 256 threads by itself: blobs written when the default was
+    // 256 threads hold the same CVs in another order
+    uint64_t magic = kStateMagic;
     int32_t K = 1;            // epoch steps
     int32_t bk_cap = 0;       // network events per pack and epoch
     uint32_t sp_cap = 0;      // spike buffer
@@ -144,7 +149,7 @@ struct StateHeader {
     uint64_t magic;
     int64_t step, n_slots, n_hh, n_syn, n_packs, n_bk, bk_cap, sp_cap, sp_user;
 };
-constexpr uint64_t kStateMagic = 0x41524233535441ull;
+
 constexpr int kStateParts = 18;
 // Bytes of each part.
 void state_part_bytes(const Lowered& L, const StateShape& sh, int64_t bytes[kStateParts]);

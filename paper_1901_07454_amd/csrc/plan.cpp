@@ -6,24 +6,29 @@
 
 namespace arbmi {
 
-Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, int64_t n_br, const arb_params& p,
-                 int64_t lds_max, int n_cu) {
-    (void)n_cu;
+Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, int64_t n_br, const arb_synapse* syn,
+                 int64_t n_syn, const arb_params& p, int64_t lds_max, int n_cu) {
     Plan pl;
     lds_max -= 256;  // static LDS of the kernels
-    // largest cell (CVs), widest branch level, longest branch, most branches
-    int64_t max_cv = 1, max_width = 1, max_len = 1, max_tasks = 1, max_tasks8 = 1;
+    // largest cell (CVs), widest branch level, longest branch, most branches,
+    // branches of all cells, most CVs with nonlinear or point currents
+    int64_t max_cv = 1, max_width = 1, max_len = 1, max_tasks = 1, max_tasks8 = 1, all_tasks8 = 0, max_nl = 0,
+            max_hh = 0;
     std::vector<int> depth, count;
+    std::vector<int64_t> n_syn_of(size_t(std::max(n_cells, 0)), 0);
+    for (int64_t q = 0; q < n_syn && syn; ++q)
+        if (syn[q].cell >= 0 && syn[q].cell < n_cells) n_syn_of[syn[q].cell]++;
     for (int32_t c = 0; c < n_cells && cells; ++c) {
         const arb_cell& C = cells[c];
         if (C.branch_begin < 0 || C.n_branch < 0 || C.branch_begin + C.n_branch > n_br) continue;
-        int64_t n = 1, seg8 = 1;
+        int64_t n = 1, seg8 = 1, hh = (C.soma_mech & ARB_MECH_HH) ? 1 : 0;
         depth.assign(C.n_branch, 0);
         count.assign(C.n_branch + 2, 0);
         for (int32_t b = 0; b < C.n_branch; ++b) {
             const arb_branch& B = br[C.branch_begin + b];
             n += std::max(0, B.n_cv);
             seg8 += (std::max(1, B.n_cv) + 7) / 8;
+            if (B.mech & ARB_MECH_HH) hh += std::max(0, B.n_cv);
             max_len = std::max<int64_t>(max_len, B.n_cv);
             depth[b] = (B.parent < 0 || B.parent >= b) ? 1 : depth[B.parent] + 1;
             if (depth[b] <= C.n_branch) count[depth[b]]++;
@@ -32,6 +37,9 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
         max_cv = std::max(max_cv, n);
         max_tasks = std::max<int64_t>(max_tasks, int64_t(C.n_branch) + 1);
         max_tasks8 = std::max(max_tasks8, seg8);
+        all_tasks8 += seg8;
+        max_hh = std::max(max_hh, hh);
+        max_nl = std::max(max_nl, p.n_densities > 0 ? n : std::min(n, hh + n_syn_of[c]));
     }
     const bool grads = (p.flags & ARB_FLAG_GRADIENTS) != 0;
 
@@ -56,14 +64,52 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
     const bool reg_ok = p.coef_mode == 3 || (p.coef_mode == 0 && max_len <= 16);
     if (reg_ok) {
         pl.coef_mode = 3;
-        pl.block_threads = p.block_threads ? p.block_threads : 256;
         pl.reg_len = (max_len > 8 && max_len <= 16) ? 16 : 8;
-        if (pl.reg_len == 8)
-            pl.reg_slots = (std::max(max_tasks, max_tasks8) <= 2 * pl.block_threads) ? 2 : 3;
-        else
-            pl.reg_slots = 1;
         pl.lds_budget = lds_max / 2;
         pl.lds_hard_max = lds_max;
+        const int64_t tasks = pl.reg_len == 8 ? std::max(max_tasks, max_tasks8) : max_tasks;
+        if (p.block_threads == 0 && p.cells_per_pack == 0) {
+            // One wave per workgroup where its register slots hold the largest
+            // cell: a step is a chain of short phases, and in one wave they
+            // follow each other without barriers (8192 cells of 1017 CVs:
+            // 12.2 us a step, against 15.6 with four cells in 256 threads;
+            // 96 of them 2.3 against 3.3).  More threads pay while there are
+            // fewer waves than the GPU has SIMDs and a cell has work for
+            // them: several rounds of branches or of nonlinear CVs per thread
+            // (256 cells of 200 hh CVs: 6.6 / 4.8 / 3.7 us a step with 64 / 128
+            // / 256 threads, 1024 of them 9.0 / 11.3 / 16.7).
+            const int64_t slots = pl.reg_len == 8 ? 3 : 1;
+            int T = 64;
+            while (T < 256 && tasks > slots * T) T *= 2;
+            const int want = (max_nl > 128 || tasks > 128) ? 256 : max_nl > 64 ? 128 : 64;
+            while (T < want && int64_t(n_cells) * (2 * T / 64) <= 4 * int64_t(n_cu)) T *= 2;
+            pl.block_threads = T;
+            pl.reg_slots = pl.reg_len == 8 ? int(std::min<int64_t>(3, std::max<int64_t>(1, (tasks + T - 1) / T))) : 1;
+            // Several cells in a workgroup only where its lanes would idle
+            // otherwise: as many average cells as its slots take, and no more
+            // nonlinear CVs than threads (two cells of 200 hh CVs in 64
+            // threads: 11.9 us a step, one 7.4).  Four cells of 16 branches in
+            // one wave cost what one costs (16,000 of them 4.1 against 11.2
+            // us a step).  Cells that differ much in size (T = 256) fill a
+            // workgroup up to half the LDS, unless every cell can have a CU.
+            if (T == 256 && tasks > slots * 128) {
+                pl.max_cells_per_pack = n_cells <= n_cu ? 1 : T;
+            } else {
+                const int64_t avg = std::max<int64_t>(1, all_tasks8 / std::max(1, n_cells));
+                int64_t c = std::min(pl.reg_slots * T / avg, T / std::max<int64_t>(1, max_nl));
+                // while that leaves SIMDs idle, no more cells than have a
+                // thread for every gate
+                const int64_t spread = kSpreadHH / std::max<int64_t>(1, max_hh);
+                if (spread >= 1 && n_cells <= 4 * int64_t(n_cu) * spread) c = std::min(c, spread);
+                pl.max_cells_per_pack = std::max<int64_t>(1, c);
+            }
+            return pl;
+        }
+        pl.block_threads = p.block_threads ? p.block_threads : 256;
+        if (pl.reg_len == 8)
+            pl.reg_slots = (tasks <= 2 * pl.block_threads) ? 2 : 3;
+        else
+            pl.reg_slots = 1;
         pl.max_cells_per_pack = p.cells_per_pack > 0 ? std::min(p.cells_per_pack, pl.block_threads) : pl.block_threads;
         if (p.cells_per_pack > 0) pl.lds_budget = lds_max;
         return pl;

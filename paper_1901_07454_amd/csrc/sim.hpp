@@ -31,8 +31,8 @@ struct Plan {
     int64_t fallback_lds_budget = 0;
     int64_t fallback_lds_hard_max = 0;
 };
-Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, int64_t n_br, const arb_params& p,
-                 int64_t lds_max, int n_cu);
+Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, int64_t n_br, const arb_synapse* syn,
+                 int64_t n_syn, const arb_params& p, int64_t lds_max, int n_cu);
 
 struct GradState;
 
