@@ -52,6 +52,9 @@ struct PackDesc {
                          // beta stay in HBM (a cell too large for LDS otherwise)
     int64_t xe0, xe1; // external events [xe0, xe1), sorted by (step, syn, input order)
     double syn_e, syn_decay;  // the shared values when syn_uniform
+    int32_t syn_sum; // syn_global packs that are syn_uniform: a launch keeps one conductance sum per
+                     // nonlinear CV in LDS (kSumMinSteps), if LDS has room for them
+    int32_t pad0;
 };
 
 // Bytes of dynamic LDS the step kernel uses for a pack.  Layout in the
@@ -65,7 +68,7 @@ struct PackDesc {
 // scalars with two spare entries each (a branch's contribution to its parent,
 // then its distal V; its contribution with no children, then its distal V
 // for a grounded parent; in packs of at most binary branch points, F_0 Q_0),
-// the nonlinear entries, the children's tasks (other packs) and the slot of
+// the conductance sum of each nonlinear CV (syn_sum), the nonlinear entries, the children's tasks (other packs) and the slot of
 // each hh instance.
 
 // Packs with at most this many hh instances give each gate its own thread
@@ -77,6 +80,18 @@ constexpr int kSpreadHH = 20;
 // too large for LDS otherwise reads its hh conductances and the step-invariant
 // right-hand side of its nonlinear CVs from HBM each step (hh_global).
 constexpr int64_t kSynLdsMax = 16384;
+
+// A pack whose HBM synapses share reversal potential and decay (syn_sum)
+// needs only the sum of each CV's conductances in a step: the sums of decaying
+// terms with one rate decay at that rate.  A launch of at least kSumMinSteps
+// steps therefore reads the conductances once, carries the sums in LDS, and
+// scales the conductances by the launch's decay once at its end: three passes
+// over them in all, against two a step streaming them (240 cells of 10,000
+// synapses, us a launch of 1, 2 and 3 steps: streaming 30, 45, 59; with sums
+// 36, 38, 40).  A single step streams.  Events enter a conductance divided by the decay since the launch's
+// start, kept above e^-kSumMaxLog.
+constexpr int kSumMinSteps = 2;
+constexpr double kSumMaxLog = 300.0;
 
 // Incoming connections a pack of several cells may have: one workgroup
 // pulls and delivers all of its pack's network events.
@@ -97,7 +112,8 @@ inline int64_t pack_lds_bytes(const PackDesc& D, int coef_mode) {
     if (coef_mode == 3) {
         const int64_t dbl = vr_block_doubles(D.nslot, D.spare) + (D.syn_global ? 0 : 3 * int64_t(D.nsyn)) +
                             (D.hh_global ? 3 : 5) * int64_t(D.nhh) +
-                            (D.hh_global ? 0 : int64_t(D.nnl)) + (D.binary ? 3 : 2) * (int64_t(D.ntk) + 2);
+                            (D.hh_global ? 0 : int64_t(D.nnl)) + (D.binary ? 3 : 2) * (int64_t(D.ntk) + 2) +
+                            (D.syn_sum ? int64_t(D.nnl) : 0);
         return 8 * dbl + 16 * int64_t(D.nnl) + (D.binary ? 0 : 4 * int64_t(D.nch)) + 4 * int64_t(D.nhh);
     }
     const bool cl = coef_mode == 1;

@@ -867,6 +867,10 @@ int lower_model(const arb_cell* cells, int32_t n_cells, const arb_branch* br, in
         D.nic = int32_t(L.ic_on.size()) - D.ic0;
         D.nhh = int32_t(L.hh_cv.size()) - D.hh0;
         D.nsyn = int32_t(L.syn_global.size()) - D.syn0;
+        if (D.syn_global && D.syn_uniform && D.syn_decay > 0.0) {
+            D.syn_sum = 1;
+            if (pack_lds_bytes(D, L.coef_mode) > opt.lds_hard_max) D.syn_sum = 0;
+        }
         if (n_den > 0 && (D.syn_global || D.hh_global) && L.gen_pk.back() != int32_t(L.gen_mech.size())) {
             err = "generated mechanisms do not run on a cell whose state is held in HBM (too large for LDS)";
             return ARB_EINVAL;
@@ -894,6 +898,25 @@ int lower_model(const arb_cell* cells, int32_t n_cells, const arb_branch* br, in
         L.reg_slots = used;
     }
 
+    // The order in which a step's events of different synapses are stored:
+    // by position, or in packs with conductance sums by CV (then by position),
+    // so that the events of one CV are adjacent.  Position + ord_shift[position]
+    // is a synapse's place in it; packs stay contiguous.
+    std::vector<int32_t> ord_shift;
+    for (const PackDesc& D : L.packs) {
+        if (!D.syn_sum) continue;
+        if (ord_shift.empty()) ord_shift.assign(L.syn_global.size(), 0);
+        int64_t at = D.syn0;
+        for (int64_t j = D.nl0; j < int64_t(D.nl0) + D.nnl; ++j) {
+            const int64_t w = std::min<int64_t>(T, D.nnl - ((j - D.nl0) / T) * T);
+            const int64_t u0 = ((j - D.nl0) / T) * T;
+            const int64_t end = (u0 + T < D.nnl) ? L.nl[D.nl0 + u0 + T].syn0 : D.nsyn;
+            for (int64_t pos = L.nl[j].syn0; pos < end; pos += w)  // padding included
+                ord_shift[size_t(D.syn0 + pos)] = int32_t(at++ - (D.syn0 + pos));
+        }
+    }
+    auto order_of = [&](int64_t pos) { return ord_shift.empty() ? pos : pos + ord_shift[size_t(pos)]; };
+
     // external events, grouped per pack, ordered (step, pack synapse, input order)
     {
         std::vector<int64_t> idx(n_ev);
@@ -904,7 +927,7 @@ int lower_model(const arb_cell* cells, int32_t n_cells, const arb_branch* br, in
             if (pa != pb) return pa < pb;
             if (opt.ev_t_ms && opt.ev_t_ms[a] != opt.ev_t_ms[b]) return opt.ev_t_ms[a] < opt.ev_t_ms[b];
             if (ev[a].step != ev[b].step) return ev[a].step < ev[b].step;
-            const int64_t sa = L.syn_pack_index[ev[a].syn], sb = L.syn_pack_index[ev[b].syn];
+            const int64_t sa = order_of(L.syn_pack_index[ev[a].syn]), sb = order_of(L.syn_pack_index[ev[b].syn]);
             if (sa != sb) return sa < sb;
             return a < b;
         });
@@ -928,7 +951,7 @@ int lower_model(const arb_cell* cells, int32_t n_cells, const arb_branch* br, in
         }
     }
 
-    // connections: rank by (dst pack, pack synapse, src, index).
+    // connections: rank by (dst pack, pack synapse in the order above, src, index).
     // A pack's synapse positions are contiguous and packs follow each other,
     // so ordering by position orders by pack: a counting sort by position
     // (stable, so by index within a position), then by source where several
@@ -936,12 +959,13 @@ int lower_model(const arb_cell* cells, int32_t n_cells, const arb_branch* br, in
     {
         const size_t npos = L.syn_global.size();
         std::vector<int64_t> at(npos + 1, 0);
-        for (int64_t q = 0; q < n_conn; ++q) at[size_t(L.syn_pack_index[conn[q].syn]) + 1]++;
+        auto place = [&](int64_t q) { return size_t(order_of(L.syn_pack_index[conn[q].syn])); };
+        for (int64_t q = 0; q < n_conn; ++q) at[place(q) + 1]++;
         for (size_t k = 0; k < npos; ++k) at[k + 1] += at[k];
         std::vector<int64_t> idx(n_conn);
         {
             std::vector<int64_t> fill(at.begin(), at.end() - 1);
-            for (int64_t q = 0; q < n_conn; ++q) idx[size_t(fill[size_t(L.syn_pack_index[conn[q].syn])]++)] = q;
+            for (int64_t q = 0; q < n_conn; ++q) idx[size_t(fill[place(q)]++)] = q;
         }
         for (size_t k = 0; k < npos; ++k)
             if (at[k + 1] - at[k] > 1)

@@ -97,9 +97,27 @@ __global__ void __launch_bounds__(T, REC ? ((S * L <= 8) ? 2 : 1) : ((S * L <= 8
     double* sF = sC + (pk.ntk + 2);
     double* sY = sF;
     double* sQ = sF + (pk.ntk + 2);
-    NlDesc* s_nl = reinterpret_cast<NlDesc*>(sQ + (pk.binary ? pk.ntk + 2 : 0));
+    double* s_sum = sQ + (pk.binary ? pk.ntk + 2 : 0);         // conductance sums (syn_sum)
+    NlDesc* s_nl = reinterpret_cast<NlDesc*>(s_sum + (G && pk.syn_sum ? pk.nnl : 0));
     int32_t* s_ch = reinterpret_cast<int32_t*>(s_nl + pk.nnl);  // children's tasks (other packs)
     int32_t* s_hhs = s_ch + (pk.binary ? 0 : pk.nch);          // per hh instance: its CV's slot
+
+    // One conductance sum per nonlinear CV for the launch (kSumMinSteps in
+    // layout.hpp), instead of streaming every conductance each step, which
+    // took 15,500 of 19,800 cycles a step (10,000 synapses a cell: 77 read and
+    // written in series by each of the 130 threads that have a CV; at 8192
+    // cells, the whole HBM rate).  Only events then touch HBM during a step.
+    // 240 cells x 10,000 synapses, all connected: 13.6 us a step streaming,
+    // 3.5 with the sums.
+    const bool sums = G && syn_hbm && pk.syn_sum && a.nsteps >= kSumMinSteps &&
+                      a.nsteps * -log(pk.syn_decay) <= kSumMaxLog;
+    double since = 1.0;  // the decay since the launch's start
+    // the nonlinear entry of a synapse (groups of T entries, interleaved)
+    auto entry_of = [&](int q) {
+        int u0 = 0;
+        while (u0 + T < pk.nnl && q >= s_nl[u0 + T].syn0) u0 += T;
+        return u0 + (q - s_nl[u0].syn0) % min(T, pk.nnl - u0);
+    };
 
     const bool rec = REC && a.rec_V != nullptr;
     for (int i = tid; i < ns; i += T) {
@@ -190,6 +208,22 @@ __global__ void __launch_bounds__(T, REC ? ((S * L <= 8) ? 2 : 1) : ((S * L <= 8
     __syncthreads();
     // the V entry of this thread's gate in the spread update, fixed for the launch
     const int hv = (pk.nhh <= kSpreadHH && tid < 3 * pk.nhh) ? s_hhs[hq] : 0;
+    if (sums) {
+        for (int j = tid; j < pk.nnl; j += T) {
+            const NlDesc d = s_nl[j];
+            const int w = min(T, pk.nnl - (j / T) * T);
+            double s = 0.0;
+            for (int k0 = 0; k0 < d.nsyn; k0 += 8) {  // eight loads in flight
+                double gg[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) gg[i] = g_g[d.syn0 + min(k0 + i, d.nsyn - 1) * w];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) s += (k0 + i < d.nsyn) ? gg[i] : 0.0;
+            }
+            s_sum[j] = s;
+        }
+        __syncthreads();
+    }
 
     for (int s = 0; s < a.nsteps; ++s) {
         const int64_t n = step0 + s;
@@ -205,6 +239,7 @@ __global__ void __launch_bounds__(T, REC ? ((S * L <= 8) ? 2 : 1) : ((S * L <= 8
         if (int32_t(n - estart) == eb) {
             const uint32_t i0 = eoff[eb], i1 = eoff[eb + 1];
             eb = int32_t(enxt[eb + 1]);
+            const double scale = sums ? 1.0 / since : 1.0;
             for (uint32_t c = i0; c < i1; c += 4 * T) {
                 int q[4];
                 double w[4], gq[4];
@@ -226,10 +261,43 @@ __global__ void __launch_bounds__(T, REC ? ((S * L <= 8) ? 2 : 1) : ((S * L <= 8
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
                     if (head[u]) {
-                        double x = gq[u] + w[u];
-                        for (uint32_t j = c + uint32_t(u * T + tid) + 1; j < i1 && eq[j] == q[u]; ++j) x += ew[j];
+                        double x = gq[u] + (sums ? w[u] * scale : w[u]);
+                        for (uint32_t j = c + uint32_t(u * T + tid) + 1; j < i1 && eq[j] == q[u]; ++j)
+                            x += sums ? ew[j] * scale : ew[j];
                         sgv[q[u]] = x;
                     }
+                if (sums) {
+                    // the CV's sum: the thread with the first of its adjacent
+                    // events adds them all, in order
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const uint32_t i = c + uint32_t(u * T + tid);
+                        if (i >= i1) continue;
+                        const int e = entry_of(q[u]);
+                        if (i > i0 && entry_of(eq[i - 1]) == e) continue;
+                        double x = w[u];
+                        for (uint32_t j = i + 1; j < i1;) {  // eight events' loads in flight
+                            int qq[8];
+                            double ww[8];
+#pragma unroll
+                            for (int k = 0; k < 8; ++k) {
+                                qq[k] = eq[min(j + k, i1 - 1)];
+                                ww[k] = ew[min(j + k, i1 - 1)];
+                            }
+                            int k = 0;
+                            bool more = true;
+#pragma unroll
+                            for (int h = 0; h < 8; ++h) {
+                                more = more && j + h < i1 && entry_of(qq[h]) == e;
+                                x += more ? ww[h] : 0.0;
+                                k += more ? 1 : 0;
+                            }
+                            j += 8;
+                            if (k < 8) break;
+                        }
+                        atomicAdd(&s_sum[e], x);
+                    }
+                }
             }
             if (syn_hbm) __threadfence_block();
             round_sync<T>();
@@ -241,11 +309,21 @@ __global__ void __launch_bounds__(T, REC ? ((S * L <= 8) ? 2 : 1) : ((S * L <= 8
                 const bool due = i < pk.xe1 && a.xe_step[i] == n;
                 if (due) {
                     const int q = a.xe_syn[i];
+                    const double scale = sums ? 1.0 / since : 1.0;
                     if (i == first || a.xe_syn[i - 1] != q) {
-                        double gq = sgv[q] + a.xe_w[i];
+                        double gq = sgv[q] + (sums ? a.xe_w[i] * scale : a.xe_w[i]);
                         for (int64_t j = i + 1; j < pk.xe1 && a.xe_step[j] == n && a.xe_syn[j] == q; ++j)
-                            gq += a.xe_w[j];
+                            gq += sums ? a.xe_w[j] * scale : a.xe_w[j];
                         sgv[q] = gq;
+                    }
+                    if (sums) {
+                        const int e = entry_of(q);
+                        if (i == first || entry_of(a.xe_syn[i - 1]) != e) {
+                            double x = a.xe_w[i];
+                            for (int64_t j = i + 1; j < pk.xe1 && a.xe_step[j] == n && entry_of(a.xe_syn[j]) == e; ++j)
+                                x += a.xe_w[j];
+                            atomicAdd(&s_sum[e], x);
+                        }
                     }
                 }
                 const int cnt = block_count<T>(due);
@@ -298,6 +376,10 @@ __global__ void __launch_bounds__(T, REC ? ((S * L <= 8) ? 2 : 1) : ((S * L <= 8
                     I += gq * (v - eq);
                     sg[q] = gq * dq;
                 }
+            } else if (sums) {
+                const double s = s_sum[j];
+                I += s * (v - pk.syn_e);
+                s_sum[j] = s * pk.syn_decay;
             } else {
                 // HBM synapses, interleaved over the threads of this group
                 // of entries (stride w), four at a time so their loads
@@ -444,10 +526,16 @@ __global__ void __launch_bounds__(T, REC ? ((S * L <= 8) ? 2 : 1) : ((S * L <= 8
             }
             __threadfence_block();  // before the next step's currents read them
         }
-        if (syn_hbm) __threadfence_block();  // phase B's g stores before the next step's events
+        if (sums)
+            since *= pk.syn_decay;
+        else if (syn_hbm)
+            __threadfence_block();  // phase B's g stores before the next step's events
         round_sync<T>();
     }
 
+    if (sums) {  // every event's store is ordered before this by its step's fence and barrier
+        for (int i = tid; i < pk.nsyn; i += T) g_g[i] *= since;
+    }
     for (int i = tid; i < ns; i += T) a.V[pk.slot0 + i] = sV[vix(i)];
     for (int i = tid; i < nsyn_lds; i += T) g_g[i] = sg[i];
     for (int i = tid; i < pk.nhh; i += T) {
