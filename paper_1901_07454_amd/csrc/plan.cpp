@@ -13,7 +13,7 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
     // largest cell (CVs), widest branch level, longest branch, most branches,
     // branches of all cells, most CVs with nonlinear or point currents
     int64_t max_cv = 1, max_width = 1, max_len = 1, max_tasks = 1, max_tasks8 = 1, all_tasks8 = 0, max_nl = 0,
-            max_hh = 0;
+            max_hh = 0, max_lds = 1;
     std::vector<int> depth, count;
     std::vector<int64_t> n_syn_of(size_t(std::max(n_cells, 0)), 0);
     for (int64_t q = 0; q < n_syn && syn; ++q)
@@ -39,7 +39,11 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
         max_tasks8 = std::max(max_tasks8, seg8);
         all_tasks8 += seg8;
         max_hh = std::max(max_hh, hh);
-        max_nl = std::max(max_nl, p.n_densities > 0 ? n : std::min(n, hh + n_syn_of[c]));
+        const int64_t nl = p.n_densities > 0 ? n : std::min(n, hh + n_syn_of[c]);
+        max_nl = std::max(max_nl, nl);
+        // the register layout's LDS of the cell, near enough (pack_lds_bytes)
+        const int64_t syn_lds = 24 * n_syn_of[c] > kSynLdsMax ? 0 : 24 * n_syn_of[c];
+        max_lds = std::max(max_lds, (128 + 24) * seg8 + syn_lds + 44 * hh + (p.n_densities > 0 ? 37 : 24) * nl);
     }
     const bool grads = (p.flags & ARB_FLAG_GRADIENTS) != 0;
 
@@ -81,6 +85,21 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
             const int64_t slots = pl.reg_len == 8 ? 3 : 1;
             int T = 64;
             while (T < 256 && tasks > slots * T) T *= 2;
+            // Where LDS holds few of these cells per CU and they have several
+            // nonlinear CVs for each thread, two waves per SIMD by threads
+            // (1024 cells with every CV hh: 505 CVs, 44 KB: 26.0 / 16.8 / 11.1
+            // us a step with 64 / 128 / 256 threads; 249 CVs, 22 KB: 7.5 / 6.8
+            // / 7.5).
+            while (T < 256 && max_nl > T && (lds_max / max_lds) * (T / 64) < 8) T *= 2;
+            // two such cells of more than 64 branches share 256 threads
+            // better than they fill 128 each (2048 cells of 1017 CVs, a
+            // quarter of them hh: 15.9 against 18.0 us a step), while there are
+            // more of them than CUs take at once (512 cells: 6.6 against 6.0)
+            int64_t pair = 0;
+            if (T == 128 && max_nl > 128 && tasks > 64 && tasks <= 128) {
+                T = 256;
+                pair = int64_t(n_cells) * (T / 64) <= 8 * int64_t(n_cu) ? 1 : 2;
+            }
             const int want = (max_nl > 128 || tasks > 128) ? 256 : max_nl > 64 ? 128 : 64;
             while (T < want && int64_t(n_cells) * (2 * T / 64) <= 4 * int64_t(n_cu)) T *= 2;
             pl.block_threads = T;
@@ -92,7 +111,9 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
             // one wave cost what one costs (16,000 of them 4.1 against 11.2
             // us a step).  Cells that differ much in size (T = 256) fill a
             // workgroup up to half the LDS, unless every cell can have a CU.
-            if (T == 256 && tasks > slots * 128) {
+            if (pair) {
+                pl.max_cells_per_pack = pair;
+            } else if (T == 256 && tasks > slots * 128) {
                 pl.max_cells_per_pack = n_cells <= n_cu ? 1 : T;
             } else {
                 const int64_t avg = std::max<int64_t>(1, all_tasks8 / std::max(1, n_cells));
