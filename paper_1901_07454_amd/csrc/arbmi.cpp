@@ -156,9 +156,9 @@ StepArgs Sim::step_args() const {
     a.threshold = L.threshold;
     a.gen_off = d_gen_off;
     a.gen_pk = d_gen_pk;
-    a.gen_row = d_gen_row;
-    a.gen_slot = d_gen_slot;
-    a.gen_w = d_gen_w;
+    a.gen_rec = d_gen_rec;
+    a.gen_rec_pk = d_gen_rec_pk;
+    a.gen_cur = d_gen_cur;
     a.gen_prm = d_gen_prm;
     a.gen_st = d_gen_st;
     a.gen_n = int64_t(L.gen_mech.size());
@@ -530,9 +530,11 @@ int build_device(Sim* s) {
     if (!L.gen_mech.empty()) {
         s->d_gen_off = dupload(s, L.gen_off, rc);
         s->d_gen_pk = dupload(s, L.gen_pk, rc);
-        s->d_gen_row = dupload(s, L.gen_row, rc);
-        s->d_gen_slot = dupload(s, L.gen_slot, rc);
-        s->d_gen_w = dupload(s, L.gen_w, rc);
+        s->d_gen_rec = dupload(s, L.gen_rec, rc);
+        s->d_gen_rec_pk = dupload(s, L.gen_rec_pk, rc);
+        for (int k = 0; k < np && !s->d_gen_cur; ++k)
+            if (!L.packs[k].ngen && L.gen_pk[k + 1] > L.gen_pk[k])
+                s->d_gen_cur = dalloc<double>(s, L.gen_mech.size(), rc);
         s->d_gen_prm = dupload(s, L.gen_prm, rc);
         s->d_gen_st = dupload(s, L.gen_st0, rc);
     }

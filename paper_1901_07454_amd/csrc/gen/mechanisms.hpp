@@ -1,82 +1,170 @@
 // GENERATED by paper_1901_07454_amd/mechgen.py from mechanisms/*.mech -- do not edit.
 // Device side of the generated mechanisms: each one's outward current
 // density at voltage v (S/cm^2 x mV; times 10 x the instance's area in um^2
-// it is in pA) and its state update over a step of dt at v.  An instance's
-// state k is st[k * ss] (states stored state-major, ss the instance count).
+// it is in pA) and its state update over a step of dt at v, for two instances
+// of one mechanism at a time.
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "../fastexp.hpp"
 #include "mechanisms_desc.hpp"
 
 namespace arbmi {
 namespace gen {
 
-__device__ __forceinline__ double gen_exprelr(double x) { return (1.0 + x == 1.0) ? 1.0 : x / expm1(x); }
+// e^x and e^x - 1 of any x from exp_pair (within 2 ulp; |x| < 700 there):
+// beyond it both saturate as the exact values do, and NaN stays NaN
+__device__ __forceinline__ ExpPair gen_exp_pair(double x) {
+    x = x > 720.0 ? 720.0 : x;
+    x = x < -750.0 ? -750.0 : x;
+    return exp_pair(x);
+}
+__device__ __forceinline__ double gen_exp(double x) { return gen_exp_pair(x).e; }
+__device__ __forceinline__ double gen_exprelr(double x) {  // free of branches
+    const double em1 = gen_exp_pair(x).em1;
+    const bool one = 1.0 + x == 1.0;
+    return (one ? 1.0 : x) / (one ? 1.0 : em1);
+}
+// x / c for a constant c: the product with its reciprocal, corrected by the
+// exact remainder (the rounded quotient, but for a last bit now and then;
+// infinities pass)
+__device__ __forceinline__ double gen_div(double x, double c) {
+    const double r = 1.0 / c, q = x * r, e = fma(-q, c, x);
+    return e == e ? fma(e, r, q) : q;
+}
 
-__device__ __forceinline__ double current(int id, double v, const double* prm, const double* st, int64_t ss) {
+// states of mechanism `id`
+__device__ __forceinline__ int n_states(int id) {
+    return id == 0 ? 1 : id == 1 ? 3 : id == 2 ? 1 : 0;
+}
+
+// hcn
+__device__ __forceinline__ double current0(double v, const double* prm, const double* st) {
+    const double gbar = prm[0];
+    const double eh = prm[1];
+    const double q = st[0];
+    return ((gbar * q) * (v - eh));
+}
+// hcn
+__device__ __forceinline__ void advance0(double v, double dt, const double* prm, double* st) {
+    const double vhalf = prm[2];
+    const double qinf = (1.0 / (1.0 + gen_exp(gen_div((v - vhalf), 6.0))));
+    const double qtau = (50.0 + (200.0 / (1.0 + gen_exp(gen_div((v + 60.0), 10.0)))));
+    { const double xinf = qinf, xtau = qtau;
+      st[0] = xinf + (st[0] - xinf) * gen_exp(-dt / xtau); }
+}
+// hh_dsl
+__device__ __forceinline__ double current1(double v, const double* prm, const double* st) {
+    const double gnabar = prm[0];
+    const double gkbar = prm[1];
+    const double gl = prm[2];
+    const double ena = prm[3];
+    const double ek = prm[4];
+    const double el = prm[5];
+    const double m = st[0];
+    const double h = st[1];
+    const double n = st[2];
+    return (((((gnabar * (m * m * m)) * h) * (v - ena)) + ((gkbar * (n * n * n * n)) * (v - ek))) + (gl * (v - el)));
+}
+// hh_dsl
+__device__ __forceinline__ void advance1(double v, double dt, const double* prm, double* st) {
+    const double am = gen_exprelr(((-(v + 40.0)) * 0.1));
+    const double bm = (4.0 * gen_exp(((-(v + 65.0)) * (1.0 / 18.0))));
+    const double ah = (0.07 * gen_exp(((-(v + 65.0)) * 0.05)));
+    const double bh = (1.0 / (gen_exp(((-(v + 35.0)) * 0.1)) + 1.0));
+    const double an = (0.1 * gen_exprelr(((-(v + 55.0)) * 0.1)));
+    const double bn = (0.125 * gen_exp(((-(v + 65.0)) * (1.0 / 80.0))));
+    { const double ra = am, rb = bm, rs = ra + rb, xinf = ra / rs;
+      st[0] = xinf + (st[0] - xinf) * gen_exp(-dt * rs); }
+    { const double ra = ah, rb = bh, rs = ra + rb, xinf = ra / rs;
+      st[1] = xinf + (st[1] - xinf) * gen_exp(-dt * rs); }
+    { const double ra = an, rb = bn, rs = ra + rb, xinf = ra / rs;
+      st[2] = xinf + (st[2] - xinf) * gen_exp(-dt * rs); }
+}
+// kdr
+__device__ __forceinline__ double current2(double v, const double* prm, const double* st) {
+    const double gbar = prm[0];
+    const double ek = prm[1];
+    const double n = st[0];
+    return ((gbar * (n * n * n * n)) * (v - ek));
+}
+// kdr
+__device__ __forceinline__ void advance2(double v, double dt, const double* prm, double* st) {
+    const double an = (0.16 * gen_exprelr(gen_div((-(v + 52.0)), 5.0)));
+    const double bn = (0.5 * gen_exp(gen_div((-(v + 57.0)), 40.0)));
+    { const double ra = an, rb = bn, rs = ra + rb, xinf = ra / rs;
+      st[0] = xinf + (st[0] - xinf) * gen_exp(-dt * rs); }
+}
+
+// two instances of mechanism `id` at voltages v[0] and v[1]: their states st
+// advanced over dt, then their current densities into cur (the bodies are
+// independent and free of branches, so they overlap)
+__device__ __forceinline__ void advance_pair(int id, const double* v, double dt, const double (*prm)[kMaxParams],
+                                             double (*st)[kMaxStates], double* cur) {
     switch (id) {
-        case 0: {  // hcn
-            const double gbar = prm[0];
-            const double eh = prm[1];
-            const double q = st[0 * ss];
-            return ((gbar * q) * (v - eh));
-        }
-        case 1: {  // hh_dsl
-            const double gnabar = prm[0];
-            const double gkbar = prm[1];
-            const double gl = prm[2];
-            const double ena = prm[3];
-            const double ek = prm[4];
-            const double el = prm[5];
-            const double m = st[0 * ss];
-            const double h = st[1 * ss];
-            const double n = st[2 * ss];
-            return (((((gnabar * (m * m * m)) * h) * (v - ena)) + ((gkbar * (n * n * n * n)) * (v - ek))) + (gl * (v - el)));
-        }
-        case 2: {  // kdr
-            const double gbar = prm[0];
-            const double ek = prm[1];
-            const double n = st[0 * ss];
-            return ((gbar * (n * n * n * n)) * (v - ek));
-        }
+        case 0:  // hcn
+            advance0(v[0], dt, prm[0], st[0]);
+            advance0(v[1], dt, prm[1], st[1]);
+            cur[0] = current0(v[0], prm[0], st[0]);
+            cur[1] = current0(v[1], prm[1], st[1]);
+            return;
+        case 1:  // hh_dsl
+            advance1(v[0], dt, prm[0], st[0]);
+            advance1(v[1], dt, prm[1], st[1]);
+            cur[0] = current1(v[0], prm[0], st[0]);
+            cur[1] = current1(v[1], prm[1], st[1]);
+            return;
+        case 2:  // kdr
+            advance2(v[0], dt, prm[0], st[0]);
+            advance2(v[1], dt, prm[1], st[1]);
+            cur[0] = current2(v[0], prm[0], st[0]);
+            cur[1] = current2(v[1], prm[1], st[1]);
+            return;
         default:
-            return 0.0;
+            cur[0] = cur[1] = 0.0;
+            return;
     }
 }
 
-__device__ __forceinline__ void advance(int id, double v, double dt, const double* prm, double* st, int64_t ss) {
+// one instance: as advance_pair's first
+__device__ __forceinline__ void advance_one(int id, double v, double dt, const double* prm, double* st, double* cur) {
     switch (id) {
-        case 0: {  // hcn
-            const double vhalf = prm[2];
-            const double qinf = (1.0 / (1.0 + exp(((v - vhalf) / 6.0))));
-            const double qtau = (50.0 + (200.0 / (1.0 + exp(((v + 60.0) / 10.0)))));
-            { const double xinf = qinf, xtau = qtau;
-              st[0 * ss] = xinf + (st[0 * ss] - xinf) * exp(-dt / xtau); }
+        case 0:  // hcn
+            advance0(v, dt, prm, st);
+            *cur = current0(v, prm, st);
             return;
-        }
-        case 1: {  // hh_dsl
-            const double am = gen_exprelr(((-(v + 40.0)) * 0.1));
-            const double bm = (4.0 * exp(((-(v + 65.0)) * (1.0 / 18.0))));
-            const double ah = (0.07 * exp(((-(v + 65.0)) * 0.05)));
-            const double bh = (1.0 / (exp(((-(v + 35.0)) * 0.1)) + 1.0));
-            const double an = (0.1 * gen_exprelr(((-(v + 55.0)) * 0.1)));
-            const double bn = (0.125 * exp(((-(v + 65.0)) * (1.0 / 80.0))));
-            { const double ra = am, rb = bm, rs = ra + rb, xinf = ra / rs;
-              st[0 * ss] = xinf + (st[0 * ss] - xinf) * exp(-dt * rs); }
-            { const double ra = ah, rb = bh, rs = ra + rb, xinf = ra / rs;
-              st[1 * ss] = xinf + (st[1 * ss] - xinf) * exp(-dt * rs); }
-            { const double ra = an, rb = bn, rs = ra + rb, xinf = ra / rs;
-              st[2 * ss] = xinf + (st[2 * ss] - xinf) * exp(-dt * rs); }
+        case 1:  // hh_dsl
+            advance1(v, dt, prm, st);
+            *cur = current1(v, prm, st);
             return;
-        }
-        case 2: {  // kdr
-            const double an = (0.16 * gen_exprelr(((-(v + 52.0)) / 5.0)));
-            const double bn = (0.5 * exp(((-(v + 57.0)) / 40.0)));
-            { const double ra = an, rb = bn, rs = ra + rb, xinf = ra / rs;
-              st[0 * ss] = xinf + (st[0 * ss] - xinf) * exp(-dt * rs); }
+        case 2:  // kdr
+            advance2(v, dt, prm, st);
+            *cur = current2(v, prm, st);
             return;
-        }
         default:
+            *cur = 0.0;
+            return;
+    }
+}
+
+// the current densities of two alone
+__device__ __forceinline__ void current_pair(int id, const double* v, const double (*prm)[kMaxParams],
+                                             const double (*st)[kMaxStates], double* cur) {
+    switch (id) {
+        case 0:  // hcn
+            cur[0] = current0(v[0], prm[0], st[0]);
+            cur[1] = current0(v[1], prm[1], st[1]);
+            return;
+        case 1:  // hh_dsl
+            cur[0] = current1(v[0], prm[0], st[0]);
+            cur[1] = current1(v[1], prm[1], st[1]);
+            return;
+        case 2:  // kdr
+            cur[0] = current2(v[0], prm[0], st[0]);
+            cur[1] = current2(v[1], prm[1], st[1]);
+            return;
+        default:
+            cur[0] = cur[1] = 0.0;
             return;
     }
 }

@@ -89,9 +89,9 @@ struct StepArgs {
     // CV, weight (10 x area, S/cm^2 -> nS), parameters and states
     const int32_t* gen_off;    // [n_nl + 1]
     const int32_t* gen_pk;     // [n_packs + 1]
-    const int32_t* gen_row;    // per instance: parameter row | catalogue index << 24
-    const int32_t* gen_slot;   // pack-local slot
-    const double* gen_w;
+    const GenRec* gen_rec;     // the order of advance
+    const int32_t* gen_rec_pk; // [n_packs + 1]
+    double* gen_cur;           // [n_inst] currents of the packs that keep them in HBM
     const double* gen_prm;     // [n_rows][kMaxParams]
     double* gen_st;            // [kMaxStates][n_inst], state-major
     int64_t gen_n;             // instances (the state-major stride)

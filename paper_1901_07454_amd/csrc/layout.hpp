@@ -54,7 +54,7 @@ struct PackDesc {
     double syn_e, syn_decay;  // the shared values when syn_uniform
     int32_t syn_sum; // syn_global packs that are syn_uniform: a launch keeps one conductance sum per
                      // nonlinear CV in LDS (kSumMinSteps), if LDS has room for them
-    int32_t pad0;
+    int32_t ngen;    // generated-mechanism instances whose currents a launch keeps in LDS (0: in HBM)
 };
 
 // Bytes of dynamic LDS the step kernel uses for a pack.  Layout in the
@@ -68,7 +68,8 @@ struct PackDesc {
 // scalars with two spare entries each (a branch's contribution to its parent,
 // then its distal V; its contribution with no children, then its distal V
 // for a grounded parent; in packs of at most binary branch points, F_0 Q_0),
-// the conductance sum of each nonlinear CV (syn_sum), the nonlinear entries, the children's tasks (other packs) and the slot of
+// the conductance sum of each nonlinear CV (syn_sum), each generated
+// instance's current (ngen), the nonlinear entries, the children's tasks (other packs) and the slot of
 // each hh instance.
 
 // Packs with at most this many hh instances give each gate its own thread
@@ -113,8 +114,9 @@ inline int64_t pack_lds_bytes(const PackDesc& D, int coef_mode) {
         const int64_t dbl = vr_block_doubles(D.nslot, D.spare) + (D.syn_global ? 0 : 3 * int64_t(D.nsyn)) +
                             (D.hh_global ? 3 : 5) * int64_t(D.nhh) +
                             (D.hh_global ? 0 : int64_t(D.nnl)) + (D.binary ? 3 : 2) * (int64_t(D.ntk) + 2) +
-                            (D.syn_sum ? int64_t(D.nnl) : 0);
-        return 8 * dbl + 16 * int64_t(D.nnl) + (D.binary ? 0 : 4 * int64_t(D.nch)) + 4 * int64_t(D.nhh);
+                            (D.syn_sum ? int64_t(D.nnl) : 0) + D.ngen;
+        return 8 * dbl + 16 * int64_t(D.nnl) + (D.binary ? 0 : 4 * int64_t(D.nch)) + 4 * int64_t(D.nhh) +
+               (D.ngen ? 4 * (int64_t(D.nnl) + 1) : 0);
     }
     const bool cl = coef_mode == 1;
     const int64_t dbl = (cl ? 6 : 2) * int64_t(D.nslot) + int64_t(D.nsyn) + 3 * int64_t(D.nhh) +
@@ -157,6 +159,19 @@ struct NlDesc {     // one CV carrying an hh instance, synapses or current clamp
     int32_t hh;     // pack-local hh instance, -1 if none
     int32_t syn0;   // pack-local synapses syn0 + k s, k < nsyn, with s = 1, or in a pack
     int32_t nsyn;   //   keeping synapses in HBM s = the entries of its group of T
+};
+
+// One place in the order in which a pack's generated instances are advanced:
+// by mechanism, each mechanism's padded to a multiple of kGenChunk (two
+// instances for each lane of a wave), so that a wave runs one mechanism's code.
+constexpr int kGenChunk = 128;
+struct GenRec {
+    int32_t row;   // parameter row | catalogue index << 24
+    int32_t slot;  // pack-local slot of the CV
+    int32_t inst;  // instance within the pack (CV order), -1: padding
+    int32_t half;  // 1: the second half of this record's chunk is padding
+    double w;      // 10 x area
+    double pad1;
 };
 
 // Device counters and flags of a sim.

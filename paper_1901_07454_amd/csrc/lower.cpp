@@ -879,6 +879,29 @@ int lower_model(const arb_cell* cells, int32_t n_cells, const arb_branch* br, in
     if (n_den > 0) {
         L.gen_off.push_back(int32_t(L.gen_mech.size()));
         L.gen_pk.push_back(int32_t(L.gen_mech.size()));
+        for (int64_t pk = 0; pk < n_packs; ++pk) {
+            PackDesc& D = L.packs[pk];
+            const int32_t q0 = L.gen_pk[pk], q1 = L.gen_pk[pk + 1];
+            L.gen_rec_pk.push_back(int32_t(L.gen_rec.size()));
+            for (int32_t mech = 0; mech < gen::kNumMechs; ++mech) {
+                int32_t last = -1;
+                for (int32_t q = q0; q < q1; ++q)
+                    if (L.gen_mech[q] == mech) {
+                        L.gen_rec.push_back({L.gen_row[q], L.gen_slot[q], q - q0, 0, L.gen_w[q], 0.0});
+                        last = q;
+                    }
+                if (last < 0) continue;
+                const size_t rem = L.gen_rec.size() % kGenChunk;
+                if (rem && rem <= kGenChunk / 2)
+                    for (size_t k = L.gen_rec.size() - rem; k < L.gen_rec.size(); ++k) L.gen_rec[k].half = 1;
+                const int32_t half = (rem && rem <= kGenChunk / 2) ? 1 : 0;
+                while (L.gen_rec.size() % kGenChunk)
+                    L.gen_rec.push_back({L.gen_row[last], L.gen_slot[last], -1, half, 0.0, 0.0});
+            }
+            D.ngen = q1 - q0;
+            if (pack_lds_bytes(D, L.coef_mode) > opt.lds_hard_max) D.ngen = 0;
+        }
+        L.gen_rec_pk.push_back(int32_t(L.gen_rec.size()));
         const size_t ni = L.gen_mech.size();
         std::vector<double> sm(L.gen_st0.size());
         for (size_t q = 0; q < ni; ++q)

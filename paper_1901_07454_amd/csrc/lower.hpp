@@ -88,6 +88,8 @@ struct Lowered {
                                               // catalogue index (high bits)
     std::vector<int32_t> gen_slot;            // per instance: pack-local slot of its CV
     std::vector<double> gen_w;                // per instance: 10 x its membrane area (um^2): S/cm^2 -> nS
+    std::vector<GenRec> gen_rec;              // the order of advance, every pack's a multiple of kGenChunk
+    std::vector<int32_t> gen_rec_pk;          // [n_packs + 1] first record of each pack
     std::vector<int32_t> gen_rmech;           // per parameter row: catalogue index (host side only)
     std::vector<double> gen_prm;              // [n_rows][gen::kMaxParams], one row per distinct
                                               // (mechanism, parameters) pair

@@ -173,22 +173,26 @@ def _num(x: float) -> str:
     return s if ("." in s or "e" in s or "inf" in s or "nan" in s) else s + ".0"
 
 
-def emit_expr(e) -> str:
+def emit_expr(e, device: bool = False) -> str:
     """C++ for an expression: every operation parenthesised, so the C++
-    evaluates exactly the tree that was written."""
+    evaluates exactly the tree that was written.  Device code calls gen_exp
+    for exp and gen_div for a division by a constant (render_device)."""
     k = e[0]
     if k == "num":
         return _num(e[1])
     if k == "var":
         return e[1]
     if k == "neg":
-        return f"(-{emit_expr(e[1])})"
+        return f"(-{emit_expr(e[1], device)})"
     if k == "call":
-        return f"{'gen_exprelr' if e[1] == 'exprelr' else e[1]}({emit_expr(e[2])})"
+        name = "gen_exprelr" if e[1] == "exprelr" else "gen_exp" if device and e[1] == "exp" else e[1]
+        return f"{name}({emit_expr(e[2], device)})"
     if k == "pow":
-        b = emit_expr(e[1])
+        b = emit_expr(e[1], device)
         return "(" + " * ".join([b] * e[2]) + ")"
-    return f"({emit_expr(e[2])} {e[1]} {emit_expr(e[3])})"
+    if device and e[1] == "/" and e[3][0] == "num" and _names(e[2]) and 1e-3 <= e[3][1] <= 1e3:
+        return f"gen_div({emit_expr(e[2], device)}, {emit_expr(e[3])})"
+    return f"({emit_expr(e[2], device)} {e[1]} {emit_expr(e[3], device)})"
 
 
 # ------------------------------------------------------------------ mechanisms
@@ -309,25 +313,25 @@ def load_catalogue(mech_dir: str = MECH_DIR) -> list[Mechanism]:
 
 # ------------------------------------------------------------------ emission
 
-def _st(i: int, strided: bool) -> str:
-    """State i of the instance: contiguous (host), or state-major with the
-    instance count ss as the stride (device)."""
-    return f"st[{i} * ss]" if strided else f"st[{i}]"
+def _st(i: int) -> str:
+    """State i of the instance."""
+    return f"st[{i}]"
 
 
-def _gate_lines(m: Mechanism, target: str, strided: bool = False) -> list[str]:
+def _gate_lines(m: Mechanism, target: str, device: bool = False) -> list[str]:
     """State updates (target 'advance') or steady states ('steady')."""
     out = []
     for g in m.gates:
-        x = _st(m.states.index(g.state), strided)
-        a, b = emit_expr(g.a), emit_expr(g.b)
+        x = _st(m.states.index(g.state))
+        a, b = emit_expr(g.a, device), emit_expr(g.b, device)
+        exp = "gen_exp" if device else "exp"
         if g.kind == "alpha_beta":
             out.append(f"{{ const double ra = {a}, rb = {b}, rs = ra + rb, xinf = ra / rs;")
-            out.append(f"  {x} = xinf + ({x} - xinf) * exp(-dt * rs); }}" if target == "advance"
+            out.append(f"  {x} = xinf + ({x} - xinf) * {exp}(-dt * rs); }}" if target == "advance"
                        else f"  {x} = xinf; }}")
         elif target == "advance":
             out.append(f"{{ const double xinf = {a}, xtau = {b};")
-            out.append(f"  {x} = xinf + ({x} - xinf) * exp(-dt / xtau); }}")
+            out.append(f"  {x} = xinf + ({x} - xinf) * {exp}(-dt / xtau); }}")
         else:
             out.append(f"{x} = {a};")
     return out
@@ -378,7 +382,7 @@ def op_count(m: Mechanism) -> int:
     return current + advance + sum(7 if g.kind == "alpha_beta" else 5 for g in m.gates)
 
 
-def _body(m: Mechanism, kind: str, strided: bool = False) -> list[str]:
+def _body(m: Mechanism, kind: str, device: bool = False) -> list[str]:
     if kind == "current":
         exprs = [m.current]
     elif kind == "steady":
@@ -387,20 +391,20 @@ def _body(m: Mechanism, kind: str, strided: bool = False) -> list[str]:
         exprs = [g.a for g in m.gates] + [g.b for g in m.gates]
     need = _used(m, exprs)
     lines = [f"const double {p} = prm[{i}];" for i, (p, _) in enumerate(m.params) if p in need]
-    lines += [f"const double {r} = {emit_expr(e)};" for r, e in m.rates if r in need]
+    lines += [f"const double {r} = {emit_expr(e, device)};" for r, e in m.rates if r in need]
     if kind == "current":
-        lines += [f"const double {s} = {_st(i, strided)};" for i, s in enumerate(m.states) if s in need]
-        lines.append(f"return {emit_expr(m.current)};")
+        lines += [f"const double {s} = {_st(i)};" for i, s in enumerate(m.states) if s in need]
+        lines.append(f"return {emit_expr(m.current, device)};")
     else:
-        lines += _gate_lines(m, kind, strided)
+        lines += _gate_lines(m, kind, device)
     return lines
 
 
-def _switch(cat: list[Mechanism], kind: str, indent: str, strided: bool = False) -> str:
+def _switch(cat: list[Mechanism], kind: str, indent: str, device: bool = False) -> str:
     out = []
     for k, m in enumerate(cat):
         out.append(f"{indent}case {k}: {{  // {m.name}")
-        out += [indent + "    " + ln for ln in _body(m, kind, strided)]
+        out += [indent + "    " + ln for ln in _body(m, kind, device)]
         if kind != "current":
             out.append(indent + "    return;")
         out.append(indent + "}")
@@ -475,33 +479,113 @@ inline void steady(int id, double v, const double* prm, double* st) {{
 """
 
 
+def _functions(cat: list[Mechanism]) -> str:
+    """Device functions of each mechanism: its current density and its states'
+    advance."""
+    out = []
+    for k, m in enumerate(cat):
+        for kind, head in (("current", f"double current{k}(double v, const double* prm, const double* st)"),
+                           ("advance", f"void advance{k}(double v, double dt, const double* prm, double* st)")):
+            out.append(f"// {m.name}\n__device__ __forceinline__ {head} {{")
+            out += ["    " + ln for ln in _body(m, kind, True)]
+            out.append("}")
+    return "\n".join(out) + "\n"
+
+
+def _cases(cat: list[Mechanism], *calls: str) -> str:
+    """A case per mechanism that makes the calls."""
+    out = []
+    for k, m in enumerate(cat):
+        out.append(f"        case {k}:  // {m.name}")
+        out += [f"            {c.format(k=k)}" for c in calls]
+        out.append("            return;")
+    return "\n".join(out)
+
+
+def _calls(cat: list[Mechanism], *calls: str) -> str:
+    """The same for both of two instances (v[h] and so on)."""
+    return _cases(cat, *(c.replace("[h]", f"[{h}]") for c in calls for h in (0, 1)))
+
+
+def _chain(cat: list[Mechanism]) -> str:
+    """The number of states of mechanism `id` as one expression."""
+    out = "0"
+    for k, m in reversed(list(enumerate(cat))):
+        out = f"id == {k} ? {len(m.states)} : {out}"
+    return out
+
+
 def render_device(cat: list[Mechanism]) -> str:
     return _HEADER + f"""// Device side of the generated mechanisms: each one's outward current
 // density at voltage v (S/cm^2 x mV; times 10 x the instance's area in um^2
-// it is in pA) and its state update over a step of dt at v.  An instance's
-// state k is st[k * ss] (states stored state-major, ss the instance count).
+// it is in pA) and its state update over a step of dt at v, for two instances
+// of one mechanism at a time.
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "../fastexp.hpp"
 #include "mechanisms_desc.hpp"
 
 namespace arbmi {{
 namespace gen {{
 
-__device__ __forceinline__ double gen_exprelr(double x) {{ return (1.0 + x == 1.0) ? 1.0 : x / expm1(x); }}
+// e^x and e^x - 1 of any x from exp_pair (within 2 ulp; |x| < 700 there):
+// beyond it both saturate as the exact values do, and NaN stays NaN
+__device__ __forceinline__ ExpPair gen_exp_pair(double x) {{
+    x = x > 720.0 ? 720.0 : x;
+    x = x < -750.0 ? -750.0 : x;
+    return exp_pair(x);
+}}
+__device__ __forceinline__ double gen_exp(double x) {{ return gen_exp_pair(x).e; }}
+__device__ __forceinline__ double gen_exprelr(double x) {{  // free of branches
+    const double em1 = gen_exp_pair(x).em1;
+    const bool one = 1.0 + x == 1.0;
+    return (one ? 1.0 : x) / (one ? 1.0 : em1);
+}}
+// x / c for a constant c: the product with its reciprocal, corrected by the
+// exact remainder (the rounded quotient, but for a last bit now and then;
+// infinities pass)
+__device__ __forceinline__ double gen_div(double x, double c) {{
+    const double r = 1.0 / c, q = x * r, e = fma(-q, c, x);
+    return e == e ? fma(e, r, q) : q;
+}}
 
-__device__ __forceinline__ double current(int id, double v, const double* prm, const double* st, int64_t ss) {{
+// states of mechanism `id`
+__device__ __forceinline__ int n_states(int id) {{
+    return {_chain(cat)};
+}}
+
+{_functions(cat)}
+// two instances of mechanism `id` at voltages v[0] and v[1]: their states st
+// advanced over dt, then their current densities into cur (the bodies are
+// independent and free of branches, so they overlap)
+__device__ __forceinline__ void advance_pair(int id, const double* v, double dt, const double (*prm)[kMaxParams],
+                                             double (*st)[kMaxStates], double* cur) {{
     switch (id) {{
-{_switch(cat, "current", "        ", True)}
+{_calls(cat, "advance{k}(v[h], dt, prm[h], st[h]);", "cur[h] = current{k}(v[h], prm[h], st[h]);")}
         default:
-            return 0.0;
+            cur[0] = cur[1] = 0.0;
+            return;
     }}
 }}
 
-__device__ __forceinline__ void advance(int id, double v, double dt, const double* prm, double* st, int64_t ss) {{
+// one instance: as advance_pair's first
+__device__ __forceinline__ void advance_one(int id, double v, double dt, const double* prm, double* st, double* cur) {{
     switch (id) {{
-{_switch(cat, "advance", "        ", True)}
+{_cases(cat, "advance{k}(v, dt, prm, st);", "*cur = current{k}(v, prm, st);")}
         default:
+            *cur = 0.0;
+            return;
+    }}
+}}
+
+// the current densities of two alone
+__device__ __forceinline__ void current_pair(int id, const double* v, const double (*prm)[kMaxParams],
+                                             const double (*st)[kMaxStates], double* cur) {{
+    switch (id) {{
+{_calls(cat, "cur[h] = current{k}(v[h], prm[h], st[h]);")}
+        default:
+            cur[0] = cur[1] = 0.0;
             return;
     }}
 }}
