@@ -10,6 +10,12 @@ namespace dev {
 
 // x / (exp(x) - 1) with its removable singularity at 0
 __device__ inline double exprelr(double x) { return (1.0 + x == 1.0) ? 1.0 : x / expm1(x); }
+// the same values without a branch, so that two evaluations can overlap
+__device__ inline double exprelr_flat(double x) {
+    const bool one = 1.0 + x == 1.0;
+    const double em1 = expm1(x);
+    return (one ? 1.0 : x) / (one ? 1.0 : em1);
+}
 
 // d/dx of x / (exp(x) - 1); a short series near the removable singularity
 __device__ inline double exprelr_dx(double x) {
@@ -22,13 +28,15 @@ __device__ inline double exprelr_dx(double x) {
 struct Rates {
     double am, bm, ah, bh, an, bn;
 };
+template <bool FLAT = false>
 __device__ inline Rates hh_rates(double v) {
     Rates r;
-    r.am = exprelr(-(v + 40.0) * 0.1);
+    const double xm = -(v + 40.0) * 0.1, xn = -(v + 55.0) * 0.1;
+    r.am = FLAT ? exprelr_flat(xm) : exprelr(xm);
     r.bm = 4.0 * exp(-(v + 65.0) * (1.0 / 18.0));
     r.ah = 0.07 * exp(-(v + 65.0) * 0.05);
     r.bh = 1.0 / (exp(-(v + 35.0) * 0.1) + 1.0);
-    r.an = 0.1 * exprelr(-(v + 55.0) * 0.1);
+    r.an = 0.1 * (FLAT ? exprelr_flat(xn) : exprelr(xn));
     r.bn = 0.125 * exp(-(v + 65.0) * (1.0 / 80.0));
     return r;
 }

@@ -90,18 +90,24 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
             // (1024 cells with every CV hh: 505 CVs, 44 KB: 26.0 / 16.8 / 11.1
             // us a step with 64 / 128 / 256 threads; 249 CVs, 22 KB: 7.5 / 6.8
             // / 7.5).
-            while (T < 256 && max_nl > T && (lds_max / max_lds) * (T / 64) < 8) T *= 2;
+            const int64_t heavy = p.n_densities > 0 ? max_nl : max_hh;  // costly ones
+            while (T < 256 && heavy > T && (lds_max / max_lds) * (T / 64) < 8) T *= 2;
             // two such cells of more than 64 branches share 256 threads
             // better than they fill 128 each (2048 cells of 1017 CVs, a
             // quarter of them hh: 15.9 against 18.0 us a step), while there are
             // more of them than CUs take at once (512 cells: 6.6 against 6.0)
             int64_t pair = 0;
-            if (T == 128 && max_nl > 128 && tasks > 64 && tasks <= 128) {
+            if (T == 128 && heavy > 128 && tasks > 64 && tasks <= 128) {
                 T = 256;
                 pair = int64_t(n_cells) * (T / 64) <= 8 * int64_t(n_cu) ? 1 : 2;
             }
             const int want = (max_nl > 128 || tasks > 128) ? 256 : max_nl > 64 ? 128 : 64;
             while (T < want && int64_t(n_cells) * (2 * T / 64) <= 4 * int64_t(n_cu)) T *= 2;
+            // Cells of more than 256 branches in 512 threads, two waves per SIMD,
+            // where the kernels have it (uneven cells of up to 5000 CVs, us a
+            // step with 256 threads / 512: 64 cells 14.2 / 11.2, 512 of them
+            // 15.2 / 12.1, 2000 of them 30.5 / 26.6).
+            if (T == 256 && tasks > 256 && tasks <= 1024 && !grads && p.n_densities == 0) T = 512;
             pl.block_threads = T;
             pl.reg_slots = pl.reg_len == 8 ? int(std::min<int64_t>(3, std::max<int64_t>(1, (tasks + T - 1) / T))) : 1;
             // Several cells in a workgroup only where its lanes would idle
@@ -113,7 +119,7 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
             // workgroup up to half the LDS, unless every cell can have a CU.
             if (pair) {
                 pl.max_cells_per_pack = pair;
-            } else if (T == 256 && tasks > slots * 128) {
+            } else if (T >= 256 && tasks > slots * 128) {
                 pl.max_cells_per_pack = n_cells <= n_cu ? 1 : T;
             } else {
                 const int64_t avg = std::max<int64_t>(1, all_tasks8 / std::max(1, n_cells));

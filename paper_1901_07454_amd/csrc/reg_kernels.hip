@@ -71,7 +71,7 @@ struct GenStates {
 // currents join the nonlinear CVs' right-hand sides, their states advance
 // with the gates; parameters and states stay in HBM).
 template <int T, int S, int L, bool G, bool REC, bool M = false>
-__global__ void __launch_bounds__(T, (REC || M) ? ((S * L <= 8) ? 2 : 1) : ((S * L <= 8) ? 3 : (S * L <= 16 ? 2 : 1)))
+__global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ? 2 : 1) : ((S * L <= 8) ? 3 : (S * L <= 16 ? 2 : 1)))
     reg_step_kernel(StepArgs a) {
     extern __shared__ __align__(16) char lds_raw[];
     const int p = blockIdx.x + a.pack0;
@@ -133,6 +133,8 @@ __global__ void __launch_bounds__(T, (REC || M) ? ((S * L <= 8) ? 2 : 1) : ((S *
     };
 
     const bool rec = REC && a.rec_V != nullptr;
+    // a thread's hh CVs two at a time: in workgroups that hold large cells
+    constexpr bool PAIRS = !REC && !M && (T == 512 || (T == 256 && (S == 3 || (S == 1 && !G))));
     for (int i = tid; i < ns; i += T) {
         const double v = a.V[pk.slot0 + i];
         sV[vix(i)] = v;
@@ -486,35 +488,69 @@ __global__ void __launch_bounds__(T, (REC || M) ? ((S * L <= 8) ? 2 : 1) : ((S *
                 }
             }
         };
-        for (int j = tid; j < pk.nnl; j += T) {
-            const NlDesc d = s_nl[j];
-            const double v = sV[vix(d.slot)];
-            double I = 0.0, bnl;
-            if (hh_hbm) {
-                bnl = a.beta[pk.slot0 + d.slot];
-                if (d.hh >= 0) {
-                    const int q = d.hh;
-                    const double m = sm[q], h = sh[q], x = sn[q];
-                    I += a.hh_gna[pk.hh0 + q] * (m * m * m * h) * (v - kENa);
-                    I += a.hh_gk[pk.hh0 + q] * (x * x * x * x) * (v - kEK);
+        if constexpr (PAIRS) {
+            // every level of an entry's dependent loads (entry, then V and
+            // gates) waited for once for two entries: 1,170 cycles an entry
+            // alone, 980 so (1460 hh CVs in 256 threads)
+            int j = tid;
+            for (; j < pk.nnl; j += 2 * T) {
+                const bool two = j + T < pk.nnl;
+                const int j2 = two ? j + T : j;
+                const NlDesc d[2] = {s_nl[j], s_nl[j2]};
+                double v[2], m[2], h[2], x[2], gna[2], gk[2], bnl[2], I[2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int q = max(d[u].hh, 0);
+                    v[u] = sV[vix(d[u].slot)];
+                    m[u] = sm[q];
+                    h[u] = sh[q];
+                    x[u] = sn[q];
+                    bnl[u] = hh_hbm ? a.beta[pk.slot0 + d[u].slot] : s_nlb[u ? j2 : j];
+                    gna[u] = hh_hbm ? a.hh_gna[pk.hh0 + q] : s_gna[q];
+                    gk[u] = hh_hbm ? a.hh_gk[pk.hh0 + q] : s_gk[q];
                 }
-            } else {
-                bnl = s_nlb[j];
-                if (d.hh >= 0) {
-                    const int q = d.hh;
-                    const double m = sm[q], h = sh[q], x = sn[q];
-                    I += s_gna[q] * (m * m * m * h) * (v - kENa);
-                    I += s_gk[q] * (x * x * x * x) * (v - kEK);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const double i = gna[u] * (m[u] * m[u] * m[u] * h[u]) * (v[u] - kENa) +
+                                     gk[u] * (x[u] * x[u] * x[u] * x[u]) * (v[u] - kEK);
+                    I[u] = d[u].hh >= 0 ? i : 0.0;
                 }
+                synapses(j, d[0], v[0], I[0]);
+                if (two) synapses(j2, d[1], v[1], I[1]);
+                sV[vix(d[0].slot) + kRoff] = bnl[0] - I[0];
+                if (two) sV[vix(d[1].slot) + kRoff] = bnl[1] - I[1];
             }
-            if constexpr (M) {
-                if (pk.ngen)
-                    for (int q = s_goff[j]; q < s_goff[j + 1]; ++q) I += s_cur[q];
-                else
-                    for (int q = a.gen_off[pk.nl0 + j]; q < a.gen_off[pk.nl0 + j + 1]; ++q) I += a.gen_cur[q];
+        } else {
+            for (int j = tid; j < pk.nnl; j += T) {
+                const NlDesc d = s_nl[j];
+                const double v = sV[vix(d.slot)];
+                double I = 0.0, bnl;
+                if (hh_hbm) {
+                    bnl = a.beta[pk.slot0 + d.slot];
+                    if (d.hh >= 0) {
+                        const int q = d.hh;
+                        const double m = sm[q], h = sh[q], x = sn[q];
+                        I += a.hh_gna[pk.hh0 + q] * (m * m * m * h) * (v - kENa);
+                        I += a.hh_gk[pk.hh0 + q] * (x * x * x * x) * (v - kEK);
+                    }
+                } else {
+                    bnl = s_nlb[j];
+                    if (d.hh >= 0) {
+                        const int q = d.hh;
+                        const double m = sm[q], h = sh[q], x = sn[q];
+                        I += s_gna[q] * (m * m * m * h) * (v - kENa);
+                        I += s_gk[q] * (x * x * x * x) * (v - kEK);
+                    }
+                }
+                if constexpr (M) {
+                    if (pk.ngen)
+                        for (int q = s_goff[j]; q < s_goff[j + 1]; ++q) I += s_cur[q];
+                    else
+                        for (int q = a.gen_off[pk.nl0 + j]; q < a.gen_off[pk.nl0 + j + 1]; ++q) I += a.gen_cur[q];
+                }
+                synapses(j, d, v, I);
+                sV[vix(d.slot) + kRoff] = bnl - I;
             }
-            synapses(j, d, v, I);
-            sV[vix(d.slot) + kRoff] = bnl - I;
         }
         if (soma >= 0) vold = sV[soma];
         if (pk.nic > 0) {
@@ -592,7 +628,31 @@ __global__ void __launch_bounds__(T, (REC || M) ? ((S * L <= 8) ? 2 : 1) : ((S *
                 x[hq] = hh_gate_step(hc, sV[hv], x[hq], a.dt);
             }
         } else {
-            for (int q = tid; q < pk.nhh; q += T) {
+            int q0 = tid;
+            if constexpr (PAIRS) {
+                // two instances at once: each is a chain of exponentials and
+                // divisions that leaves its SIMD waiting (2,570 cycles alone,
+                // 2,100 each so; 567 instances, 256 threads)
+                for (; q0 + T < pk.nhh; q0 += 2 * T) {
+                    const int q1 = q0 + T;
+                    const double v0 = sV[s_hhs[q0]], v1 = sV[s_hhs[q1]];
+                    double m0 = sm[q0], h0 = sh[q0], x0 = sn[q0], m1 = sm[q1], h1 = sh[q1], x1 = sn[q1];
+                    const Rates r0 = hh_rates<true>(v0), r1 = hh_rates<true>(v1);
+                    m0 = gate_step(m0, r0.am, r0.bm, a.dt);
+                    m1 = gate_step(m1, r1.am, r1.bm, a.dt);
+                    h0 = gate_step(h0, r0.ah, r0.bh, a.dt);
+                    h1 = gate_step(h1, r1.ah, r1.bh, a.dt);
+                    x0 = gate_step(x0, r0.an, r0.bn, a.dt);
+                    x1 = gate_step(x1, r1.an, r1.bn, a.dt);
+                    sm[q0] = m0;
+                    sh[q0] = h0;
+                    sn[q0] = x0;
+                    sm[q1] = m1;
+                    sh[q1] = h1;
+                    sn[q1] = x1;
+                }
+            }
+            for (int q = q0; q < pk.nhh; q += T) {
                 const Rates rt = hh_rates(sV[s_hhs[q]]);
                 if (rec) {  // the gates before their update
                     const int64_t at = int64_t(s) * a.n_hh_total + pk.hh0 + q;
@@ -692,6 +752,23 @@ void allow_lds(int lds_max) {
     allow_lds_one<T, S, L, false, false, true>(lds_max);
 }
 
+// 512 threads: the library's choice for large cells, never with recording or
+// generated mechanisms
+template <int S>
+void allow_lds_512(int lds_max) {
+    allow_lds_one<512, S, 8, false, false>(lds_max);
+    allow_lds_one<512, S, 8, true, false>(lds_max);
+}
+template <int S>
+hipError_t launch_reg_512(const StepArgs& a, const LaunchCfg& cfg, int n_packs, hipStream_t st) {
+    if (cfg.gen || cfg.rec) return hipErrorInvalidValue;
+    if (cfg.syn_hbm)
+        hipLaunchKernelGGL((reg_step_kernel<512, S, 8, true, false>), dim3(n_packs), dim3(512), cfg.lds_bytes, st, a);
+    else
+        hipLaunchKernelGGL((reg_step_kernel<512, S, 8, false, false>), dim3(n_packs), dim3(512), cfg.lds_bytes, st, a);
+    return hipGetLastError();
+}
+
 template <int T>
 hipError_t launch_reg_T(const StepArgs& a, const LaunchCfg& cfg, int n_packs, hipStream_t st) {
     if (cfg.reg_len == 8) {
@@ -722,6 +799,8 @@ hipError_t prepare_reg_kernels(int lds_max) {
     allow_lds<256, 2, 8>(lds_max);
     allow_lds<256, 3, 8>(lds_max);
     allow_lds<256, 1, 16>(lds_max);
+    allow_lds_512<1>(lds_max);
+    allow_lds_512<2>(lds_max);
     return hipSuccess;
 }
 
@@ -730,6 +809,11 @@ hipError_t launch_reg_step(const StepArgs& a, const LaunchCfg& cfg, int n_packs,
         case 64: return launch_reg_T<64>(a, cfg, n_packs, st);
         case 128: return launch_reg_T<128>(a, cfg, n_packs, st);
         case 256: return launch_reg_T<256>(a, cfg, n_packs, st);
+        case 512:
+            if (cfg.reg_len != 8) return hipErrorInvalidValue;
+            if (cfg.reg_slots == 1) return launch_reg_512<1>(a, cfg, n_packs, st);
+            if (cfg.reg_slots == 2) return launch_reg_512<2>(a, cfg, n_packs, st);
+            return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
     }
 }

@@ -324,14 +324,22 @@ __device__ __forceinline__ void up_pass(const PackDesc& pk, Slot<L>& g0, Slot<L>
         }
     } else if (pk.binary) {
         // after round r every level from nlev - 3 - 2 r down is final
-        for (int sr = 0; 2 * sr + 1 < pk.nlev; ++sr) {
+        for (int lv = pk.nlev - 3; lv >= -1; lv -= 2) {
             Up2In u0, u1, u2;
-            u0 = up2_load<L>(g0, sF, sQ, sC);
-            if constexpr (S > 1) u1 = up2_load<L>(g1, sF, sQ, sC);
-            if constexpr (S > 2) u2 = up2_load<L>(g2, sF, sQ, sC);
-            up2_store<L>(g0, u0, sC);
-            if constexpr (S > 1) up2_store<L>(g1, u1, sC);
-            if constexpr (S > 2) up2_store<L>(g2, u2, sC);
+            // in 512 threads only the two levels that become final take part
+            // (a wave's branches are mostly of one level, so the other waves
+            // skip the round): with every slot in every round the loads fill
+            // the LDS (22 levels, two slots: 660 cycles a round, 430 so;
+            // with 256 threads the tests cost more than they save)
+            const bool b0 = T < 512 || g0.lev == lv || g0.lev == lv + 1;
+            const bool b1 = S > 1 && (T < 512 || g1.lev == lv || g1.lev == lv + 1);
+            const bool b2 = S > 2 && (T < 512 || g2.lev == lv || g2.lev == lv + 1);
+            if (b0) u0 = up2_load<L>(g0, sF, sQ, sC);
+            if (b1) u1 = up2_load<L>(g1, sF, sQ, sC);
+            if (b2) u2 = up2_load<L>(g2, sF, sQ, sC);
+            if (b0) up2_store<L>(g0, u0, sC);
+            if (b1) up2_store<L>(g1, u1, sC);
+            if (b2) up2_store<L>(g2, u2, sC);
             round_sync<T>();
         }
     } else {
@@ -364,6 +372,19 @@ __device__ __forceinline__ void grounded_store(const Slot<L>& g, double* sY, dou
 template <int T, int S, int L>
 __device__ __forceinline__ void down_pass(const PackDesc& pk, Slot<L>& g0, Slot<L>& g1, Slot<L>& g2, const double* sY,
                                           double* sX) {
+    if constexpr (T == 512 && S > 1) {  // only the two levels of the round, as going up
+        for (int lv = 1; lv < pk.nlev; lv += 2) {
+            if (g0.lev == lv || g0.lev == lv + 1) down_store<L>(g0, down_load<L>(g0, sY, sX), sX);
+            if constexpr (S > 1) {
+                if (g1.lev == lv || g1.lev == lv + 1) down_store<L>(g1, down_load<L>(g1, sY, sX), sX);
+            }
+            if constexpr (S > 2) {
+                if (g2.lev == lv || g2.lev == lv + 1) down_store<L>(g2, down_load<L>(g2, sY, sX), sX);
+            }
+            round_sync<T>();
+        }
+        return;
+    }
     for (int sr = 0; 2 * sr + 1 < pk.nlev; ++sr) {
         DownIn d0, d1, d2;
         d0 = down_load<L>(g0, sY, sX);

@@ -34,7 +34,9 @@ EDGES = [((1, 0, 0), (64, 1, 1)),          # a lone soma
          ((300, 128, 0), (128, 2, 300)),   # fewer to spare
          ((600, 128, 0), (64, 3, 600)),    # none
          ((3, 255, 0), (256, 1, 3)),
-         ((3, 256, 0), (256, 2, 3)),
+         ((3, 256, 0), (512, 1, 3)),         # more than 256 tasks: two waves per SIMD
+         ((3, 511, 0), (512, 1, 3)),
+         ((3, 512, 0), (512, 2, 3)),
          ((2, 8, 8), (128, 1, 2)),         # 65 hh CVs
          ((2, 20, 20), (256, 1, 2)),       # 161 hh CVs
          ((1100, 20, 20), (64, 1, 1100))]
@@ -48,16 +50,19 @@ def test_shape_at_the_edges(model, shape):
 
 
 def test_every_size_up_to_the_registers_has_a_plan():
-    """Cells of up to 768 branches take the register layout, as with 256
-    threads asked for; larger ones fall back to streamed coefficients."""
+    """Cells that fit 256 threads (up to 768 tasks) take the register layout,
+    as with 256 threads asked for, and up to 1024 tasks 512 threads; larger
+    ones fall back to streamed coefficients."""
     for nb in list(range(0, 40, 3)) + [126, 127, 128, 191, 192, 383, 384, 511, 512, 766, 767]:
         m = gen.assemble(_cells(1, nb), n_steps=10)
         assert _plan(m)["coef_mode"] == _plan(m, block_threads=256)["coef_mode"] == 3, nb
-    assert _plan(gen.assemble(_cells(1, 768), n_steps=10))["coef_mode"] == 2
+    assert _plan(gen.assemble(_cells(1, 1023), n_steps=10))["coef_mode"] == 3
+    assert _plan(gen.assemble(_cells(1, 1024), n_steps=10))["coef_mode"] == 2
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("model", [(3, 0, 0), (9, 15, 0), (2, 64, 0), (2, 128, 0), (2, 8, 8), (3, 20, 20)])
+@pytest.mark.parametrize("model", [(3, 0, 0), (9, 15, 0), (2, 64, 0), (2, 128, 0), (2, 8, 8), (3, 20, 20), (2, 256, 30),
+                                   (2, 520, 100), (1, 700, 9)])
 def test_default_equals_explicit_shape(model):
     """Voltages and spikes of the default shape and of 256 threads with the
     library's packing, the shape used for every model before: the same."""
