@@ -432,7 +432,7 @@ int Sim::advance(int64_t n, const RecordArgs* rec) {
 StateShape Sim::state_shape() const {
     StateShape sh;
     if (cfg.coef_mode == 3 && !timed && p.block_threads == 0 && p.cells_per_pack == 0 && cfg.block_threads != 256)
-        sh.magic = kStateMagic ^ (uint64_t(cfg.block_threads) << 56);
+        sh.magic = kStateMagic ^ (uint64_t(cfg.block_threads / 64) << 56);
     sh.K = K;
     sh.bk_cap = bk_cap;
     sh.sp_cap = sp_cap;

@@ -96,3 +96,18 @@ def test_state_blob_of_the_other_default_is_refused():
         a.set_state(b.get_state())
     a.close()
     b.close()
+
+
+@pytest.mark.gpu
+def test_state_blob_of_256_threads_is_refused_by_512():
+    """The same for the largest workgroups the library chooses."""
+    from paper_1901_07454_amd import arbmi
+    m = gen.assemble(_cells(3, 700), n_steps=10)
+    a, b = arbmi.Simulation(m), arbmi.Simulation(m, block_threads=256, cells_per_pack=1)
+    assert a.info["block_threads"] == 512
+    assert (a.info["n_packs"], a.info["n_slots"]) == (b.info["n_packs"], b.info["n_slots"])
+    a.set_state(a.get_state())
+    with pytest.raises(arbmi.ArbError):
+        a.set_state(b.get_state())
+    a.close()
+    b.close()
