@@ -212,7 +212,7 @@ def kernel_name(info: dict, timed: bool = False, generated: bool = False) -> str
         return f"var_step_kernel<{info['block_threads']}, {info['reg_slots']}, {info['reg_len']}>"
     if generated:  # the variant with generated mechanisms (state in LDS, no recording)
         return f"reg_step_kernel<{info['block_threads']}, {info['reg_slots']}, {info['reg_len']}, false, false, true>"
-    if info["coef_mode"] == 3:
+    if info["coef_mode"] == 3 or info.get("reg_slots"):  # mode 2's long branches may be cut for registers
         return (f"reg_step_kernel<{info['block_threads']}, {info['reg_slots']}, {info['reg_len']}, "
                 f"{'true' if info['syn_hbm'] else 'false'}>")
     return f"step_kernel<{info['block_threads']}, {'true' if info['coef_mode'] == 1 else 'false'}>"

@@ -201,12 +201,14 @@ typedef struct {
     int64_t step;             /* steps completed */
     int32_t epoch_steps;
     int32_t block_threads;
-    int32_t coef_mode;        /* 1 = LDS, 2 = streamed, 3 = registers */
+    int32_t coef_mode;        /* 1 = LDS, 2 = streamed, 3 = registers; also 2 with reg_slots > 0:
+                                 branches longer than the registers, cut into segments by the
+                                 library and read into registers once a launch */
     int32_t lds_bytes;        /* dynamic LDS per workgroup */
     int64_t device_bytes;     /* device memory held by the sim */
     int64_t bytes_per_step;   /* algorithmic HBM bytes one step must move (SoA model) */
-    int32_t reg_slots;        /* coef_mode 3: branches per thread held in registers */
-    int32_t reg_len;          /* coef_mode 3: CVs per branch held in registers */
+    int32_t reg_slots;        /* branches per thread held in registers; 0 if none are */
+    int32_t reg_len;          /* CVs per branch held in registers; 0 if none are */
     int32_t syn_hbm;          /* coef_mode 3: 1 if some workgroup keeps state in HBM: its synapse
                                  state (too many synapses for LDS; streamed every step, or once
                                  a launch where the synapses share reversal potential and

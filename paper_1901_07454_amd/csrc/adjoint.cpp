@@ -101,6 +101,10 @@ int setup(Sim* s, int64_t n, int64_t k) {
         for (const Part& q : state_parts(s)) G.state_bytes += (q.bytes + 255) & ~int64_t(255);
         // adjoint LDS must fit
         G.reg = s->cfg.coef_mode == 3;
+        if (s->long_cut && !s->cfg.rec) {  // packed for the adjoint (lower_planned): record from here on
+            s->cfg.rec = 1;
+            s->graph_dirty = true;
+        }
         if (G.reg && !s->cfg.rec)
             return set_error(ARB_ESTATE, "gradients of a register-layout sim need ARB_FLAG_GRADIENTS at build");
         int64_t lds = 0;

@@ -433,6 +433,7 @@ StateShape Sim::state_shape() const {
     StateShape sh;
     if (cfg.coef_mode == 3 && !timed && p.block_threads == 0 && p.cells_per_pack == 0 && cfg.block_threads != 256)
         sh.magic = kStateMagic ^ (uint64_t(cfg.block_threads / 64) << 56);
+    if (long_cut) sh.magic = kStateMagic ^ (uint64_t(cfg.block_threads / 64 + 128) << 56);  // streamed before
     sh.K = K;
     sh.bk_cap = bk_cap;
     sh.sp_cap = sp_cap;
@@ -619,6 +620,37 @@ int build_device(Sim* s) {
 
 namespace arbmi {
 
+// Lowers a fixed-step model as planned.  A cell too large for LDS- or
+// register-resident coefficients gets them streamed, where the mode is the
+// library's choice.  Long branches cut by the library's choice are lowered
+// as for gradients (state in LDS, packs that fit the adjoint kernel): what
+// streaming takes, gradients of a sim built without their flag included, is
+// taken, and nothing more.
+static int lower_planned(const ModelView& m, const arb_params& p, const Plan& plan, LowerOptions& opt, Lowered& L,
+                         bool& long_cut, std::string& err) {
+    auto lower = [&] {
+        return lower_model(m.cells, m.n_cells, m.br, m.n_br, m.syn, m.n_syn, m.conn, m.n_conn, m.ev, m.n_ev, m.ic,
+                           m.n_ic, p, opt, L, err);
+    };
+    opt.grads = opt.grads || plan.long_cut;
+    int rc = lower();
+    long_cut = plan.long_cut && rc == ARB_OK;
+    const bool auto_mode = p.coef_mode == 0 || (p.flags & ARB_FLAG_AUTOTUNE);
+    if (rc == ARB_EINVAL && auto_mode && opt.coef_mode != 2 &&
+        (err.find("LDS") != std::string::npos || err.find("register") != std::string::npos)) {
+        opt.coef_mode = 2;
+        opt.reg_slots = 0;
+        opt.block_threads = p.block_threads ? p.block_threads : 256;
+        opt.max_cells_per_pack = std::max<int64_t>(1, plan.fallback_cells_per_pack);
+        opt.lds_budget = plan.fallback_lds_budget;
+        opt.lds_hard_max = plan.fallback_lds_hard_max;
+        opt.grads = (p.flags & ARB_FLAG_GRADIENTS) != 0;
+        L = Lowered();
+        rc = lower();
+    }
+    return rc;
+}
+
 int build_sim(const ModelView& m, const arb_params& pp, const DeviceLimits& d, Sim** out, std::string& err) {
     const arb_params* p = &pp;
     *out = nullptr;
@@ -667,22 +699,7 @@ int build_sim(const ModelView& m, const arb_params& pp, const DeviceLimits& d, S
                 break;
         }
     } else {
-        rc = lower_model(m.cells, m.n_cells, m.br, m.n_br, m.syn, m.n_syn, m.conn, m.n_conn, m.ev, m.n_ev, m.ic,
-                         m.n_ic, *p, opt, s->L, err);
-    }
-    const bool auto_mode = p->coef_mode == 0 || (p->flags & ARB_FLAG_AUTOTUNE);
-    if (rc == ARB_EINVAL && auto_mode && !timed && opt.coef_mode != 2 &&
-        (err.find("LDS") != std::string::npos || err.find("register") != std::string::npos)) {
-        // a cell too large for LDS- or register-resident coefficients: stream them
-        opt.coef_mode = 2;
-        opt.reg_slots = 0;
-        opt.block_threads = p->block_threads ? p->block_threads : 256;
-        opt.max_cells_per_pack = std::max<int64_t>(1, plan.fallback_cells_per_pack);
-        opt.lds_budget = plan.fallback_lds_budget;
-        opt.lds_hard_max = plan.fallback_lds_hard_max;
-        s->L = Lowered();
-        rc = lower_model(m.cells, m.n_cells, m.br, m.n_br, m.syn, m.n_syn, m.conn, m.n_conn, m.ev, m.n_ev, m.ic,
-                         m.n_ic, *p, opt, s->L, err);
+        rc = lower_planned(m, *p, plan, opt, s->L, s->long_cut, err);
     }
     if (rc != ARB_OK) {
         delete s;
@@ -1007,21 +1024,9 @@ int arb_plan_layout(const arb_cell* cells, int32_t n_cells, const arb_branch* br
     opt.grads = (p->flags & ARB_FLAG_GRADIENTS) != 0;
     Lowered L;
     std::string err;
-    int rc = lower_model(cells, n_cells, branches, n_branches, syn, n_syn, conn, n_conn, ev, n_ev, stim, n_stim, *p,
-                         opt, L, err);
-    const bool auto_mode = p->coef_mode == 0 || (p->flags & ARB_FLAG_AUTOTUNE);
-    if (rc == ARB_EINVAL && auto_mode && opt.coef_mode != 2 &&
-        (err.find("LDS") != std::string::npos || err.find("register") != std::string::npos)) {
-        opt.coef_mode = 2;
-        opt.reg_slots = 0;
-        opt.block_threads = p->block_threads ? p->block_threads : 256;
-        opt.max_cells_per_pack = std::max<int64_t>(1, plan.fallback_cells_per_pack);
-        opt.lds_budget = plan.fallback_lds_budget;
-        opt.lds_hard_max = plan.fallback_lds_hard_max;
-        L = Lowered();
-        rc = lower_model(cells, n_cells, branches, n_branches, syn, n_syn, conn, n_conn, ev, n_ev, stim, n_stim, *p,
-                         opt, L, err);
-    }
+    bool long_cut = false;
+    const ModelView m{cells, n_cells, branches, n_branches, syn, n_syn, conn, n_conn, ev, n_ev, stim, n_stim};
+    const int rc = lower_planned(m, *p, plan, opt, L, long_cut, err);
     if (rc != ARB_OK) return fail(rc, err);
     const std::string bad = verify_layout(L);
     if (!bad.empty()) return fail(ARB_EINVAL, "layout invariant violated: " + bad);
@@ -1036,7 +1041,7 @@ int arb_plan_layout(const arb_cell* cells, int32_t n_cells, const arb_branch* br
     I.epoch_steps = p->epoch_steps > 0 ? p->epoch_steps
                                        : (L.cr_src.empty() ? 1000 : std::min(L.min_delay, kMaxEpochSteps));
     I.block_threads = L.block_threads;
-    I.coef_mode = L.coef_mode;
+    I.coef_mode = long_cut ? 2 : L.coef_mode;
     int64_t lds = 0;
     for (const PackDesc& D : L.packs) lds = std::max(lds, pack_lds_bytes(D, L.coef_mode));
     I.lds_bytes = int32_t(lds);
@@ -1318,7 +1323,7 @@ int arb_get_info(arb_sim s_, arb_info* info) {
     I.step = s->step;
     I.epoch_steps = s->K;
     I.block_threads = s->cfg.block_threads;
-    I.coef_mode = s->cfg.coef_mode;
+    I.coef_mode = s->long_cut ? 2 : s->cfg.coef_mode;
     I.lds_bytes = s->cfg.lds_bytes;
     I.device_bytes = s->device_bytes;
     // algorithmic bytes of one step in the SoA model: per CV V read+write,

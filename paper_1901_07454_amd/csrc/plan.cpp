@@ -65,7 +65,16 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
     // cut into chains of 8-CV segments.  An explicit request is honoured or
     // refused by the lowering, never changed.  With gradients the packs must
     // also fit the register-resident adjoint kernel (the lowering checks).
-    const bool reg_ok = p.coef_mode == 3 || (p.coef_mode == 0 && max_len <= 16);
+    // The same cut is the default for longer branches, where the caller left
+    // everything to the library: streamed, a step walks each branch as one
+    // chain of CVs, whose length bounds it (64 cells of 7 sections of 27 CVs:
+    // 16.4 us a step streamed, 2.3 cut into segments; 8192 of them 22.5 / 5.5,
+    // with every CV hh 75 / 31; one cell of a 2000-CV cable 363 / 26).  Up to
+    // the segments that 256 threads hold, whose packs fit the adjoint's LDS
+    // (lower_planned).  arb_get_info still says coef_mode 2 for them.
+    pl.long_cut = p.coef_mode == 0 && max_len > 16 && p.block_threads == 0 && p.cells_per_pack == 0 && !grads &&
+                  !(p.flags & ARB_FLAG_AUTOTUNE) && max_tasks8 <= 768;
+    const bool reg_ok = p.coef_mode == 3 || (p.coef_mode == 0 && max_len <= 16) || pl.long_cut;
     if (reg_ok) {
         pl.coef_mode = 3;
         pl.reg_len = (max_len > 8 && max_len <= 16) ? 16 : 8;
@@ -107,7 +116,7 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
             // where the kernels have it (uneven cells of up to 5000 CVs, us a
             // step with 256 threads / 512: 64 cells 14.2 / 11.2, 512 of them
             // 15.2 / 12.1, 2000 of them 30.5 / 26.6).
-            if (T == 256 && tasks > 256 && tasks <= 1024 && !grads && p.n_densities == 0) T = 512;
+            if (T == 256 && tasks > 256 && tasks <= 1024 && !grads && !pl.long_cut && p.n_densities == 0) T = 512;
             pl.block_threads = T;
             pl.reg_slots = pl.reg_len == 8 ? int(std::min<int64_t>(3, std::max<int64_t>(1, (tasks + T - 1) / T))) : 1;
             // Several cells in a workgroup only where its lanes would idle

@@ -27,6 +27,7 @@ struct Plan {
     int64_t lds_hard_max = 160 * 1024;
     int64_t max_cells_per_pack = 64;
     int reg_slots = 0, reg_len = 8;
+    bool long_cut = false;  // branches longer than the registers, cut by the library's choice
     int64_t fallback_cells_per_pack = 1;  // streamed mode, if the chosen layout fails
     int64_t fallback_lds_budget = 0;
     int64_t fallback_lds_hard_max = 0;
@@ -126,6 +127,8 @@ struct Sim : arb_sim_ {
     hipStream_t st_capture = nullptr;  // capture happens here; replays go on st
     bool graph_dirty = true;
     int capture_epoch_graph();
+    // branches longer than the registers, cut into segments by the library's choice
+    bool long_cut = false;
     // variable time step (continuous event times; arb_build_cells_timed)
     bool timed = false;
     double *d_xe_t = nullptr, *d_bk_t = nullptr, *d_cr_delay_ms = nullptr;
