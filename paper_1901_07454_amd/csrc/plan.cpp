@@ -117,6 +117,15 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
             // step with 256 threads / 512: 64 cells 14.2 / 11.2, 512 of them
             // 15.2 / 12.1, 2000 of them 30.5 / 26.6).
             if (T == 256 && tasks > 256 && tasks <= 1024 && !grads && !pl.long_cut && p.n_densities == 0) T = 512;
+            // Cells with generated mechanisms and more nonlinear CVs than 256
+            // threads, where each has a CU to itself (by number, or by LDS):
+            // a step is mostly visits of their instances, in series per
+            // thread (256 cells: 1017 CVs 8.7 us a step with 256 threads, 7.7
+            // with 512; 2041 CVs 13.0 / 10.8; 505 CVs 6.3 / 6.1; 249 CVs 5.4 /
+            // 6.0).
+            if (T == 256 && p.n_densities > 0 && pl.reg_len == 8 && max_nl > 256 && tasks <= 512 &&
+                (n_cells <= n_cu || 2 * max_lds > lds_max))
+                T = 512;
             pl.block_threads = T;
             pl.reg_slots = pl.reg_len == 8 ? int(std::min<int64_t>(3, std::max<int64_t>(1, (tasks + T - 1) / T))) : 1;
             // Several cells in a workgroup only where its lanes would idle

@@ -752,17 +752,22 @@ void allow_lds(int lds_max) {
     allow_lds_one<T, S, L, false, false, true>(lds_max);
 }
 
-// 512 threads: the library's choice for large cells, never with recording or
-// generated mechanisms
+// 512 threads: the library's choice for large cells and for few cells with
+// generated mechanisms (one slot), never with recording
 template <int S>
 void allow_lds_512(int lds_max) {
     allow_lds_one<512, S, 8, false, false>(lds_max);
     allow_lds_one<512, S, 8, true, false>(lds_max);
+    if constexpr (S == 1) allow_lds_one<512, S, 8, false, false, true>(lds_max);
 }
 template <int S>
 hipError_t launch_reg_512(const StepArgs& a, const LaunchCfg& cfg, int n_packs, hipStream_t st) {
-    if (cfg.gen || cfg.rec) return hipErrorInvalidValue;
-    if (cfg.syn_hbm)
+    if (cfg.rec || (cfg.gen && (S > 1 || cfg.syn_hbm))) return hipErrorInvalidValue;
+    if (cfg.gen) {
+        if constexpr (S == 1)
+            hipLaunchKernelGGL((reg_step_kernel<512, S, 8, false, false, true>), dim3(n_packs), dim3(512),
+                               cfg.lds_bytes, st, a);
+    } else if (cfg.syn_hbm)
         hipLaunchKernelGGL((reg_step_kernel<512, S, 8, true, false>), dim3(n_packs), dim3(512), cfg.lds_bytes, st, a);
     else
         hipLaunchKernelGGL((reg_step_kernel<512, S, 8, false, false>), dim3(n_packs), dim3(512), cfg.lds_bytes, st, a);

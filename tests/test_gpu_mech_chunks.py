@@ -37,3 +37,23 @@ def test_chunks_of_instances_at_their_edges(T, n_hh_branches):
         sim.close()
     assert np.max(np.abs(out[0] - ref.state()["V"])) <= TOL
     assert np.array_equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("nb,T", [(31, 256), (32, 512), (70, 512)])
+def test_default_threads(nb, T):
+    """The library's choice: 512 threads from 257 CVs on; results as the oracle's."""
+    from paper_1901_07454_amd import arbmi
+    d = models.bare_cell([-1] + [(b - 1) // 2 for b in range(1, nb)], [8] * nb, [150.0] * nb, [2.0] * nb)
+    d.syn.append((-1, 0, 2.0, 0.0))
+    d.ext += [(0, 5, 0.05), (0, 200, 0.05)]
+    dens = [(0, b, "hh_dsl", {"gnabar": 0.04, "gkbar": 0.012}) for b in range(nb // 2)]
+    dens += [(0, b, "kdr", {"gbar": 2e-3}) for b in range(nb // 3, nb)]
+    m = gen.with_densities(gen.assemble([d], n_steps=300), dens)
+    ref = oracle.Sim(m)
+    ref.run(300)
+    sim = arbmi.Simulation(m)
+    assert sim.info["block_threads"] == T
+    sim.step(300)
+    V = sim.voltages_host()
+    sim.close()
+    assert np.max(np.abs(V - ref.state()["V"])) <= TOL
