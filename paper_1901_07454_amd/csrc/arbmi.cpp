@@ -272,7 +272,7 @@ int Sim::launch_pull(int64_t epoch, const int64_t* epoch_ptr) {
     x.epoch = epoch;
     x.bk_cap = bk_cap;
     x.epoch_steps = K;
-    HIP_TRY(launch_pull_events(x, int32_t(L.packs.size()), st));
+    HIP_TRY(launch_pull_events(x, int32_t(L.packs.size()), L.max_in_per_pack, st));
     return ARB_OK;
 }
 

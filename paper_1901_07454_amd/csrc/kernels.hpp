@@ -168,7 +168,8 @@ struct PullArgs {
     int32_t bk_cap;
     int32_t epoch_steps;       // K: LDS holds one counter per step
 };
-hipError_t launch_pull_events(const PullArgs& a, int32_t n_packs, hipStream_t st);
+// max_in: connections of the busiest pack
+hipError_t launch_pull_events(const PullArgs& a, int32_t n_packs, int64_t max_in, hipStream_t st);
 
 // dst[i] = V[perm[i]] for i < n
 hipError_t launch_gather(const double* V, const int64_t* perm, double* dst, int64_t n, hipStream_t st);
