@@ -157,13 +157,15 @@ typedef struct {
     int64_t spike_capacity;   /* spikes kept between arb_get_spikes calls; 0 = default */
     int64_t event_capacity;   /* network events per (cell pack, epoch); 0 = 4 x the busiest
                                  pack's incoming connections */
-    int32_t block_threads;    /* threads per cell pack; 0 = autotuned */
-    int32_t coef_mode;        /* 0 = autotuned, 1 = per-CV coefficients in LDS, 2 = streamed,
+    int32_t block_threads;    /* threads per cell pack: 64, 128 or 256; 0 = the library's choice
+                                 (which may be 512) */
+    int32_t coef_mode;        /* 0 = the library's choice, 1 = per-CV coefficients in LDS, 2 = streamed,
                                  3 = held in registers (by default for branches of <= 16 CVs;
-                                 on request longer branches are cut into chains of 8-CV
-                                 segments; with ARB_FLAG_GRADIENTS the packs must also fit
-                                 the register-resident adjoint kernel) */
-    int32_t cells_per_pack;   /* most cells one workgroup advances; 0 = autotuned */
+                                 longer branches are cut into chains of 8-CV segments on request,
+                                 and by default where block_threads and cells_per_pack are left to
+                                 the library too and the segments fit; with ARB_FLAG_GRADIENTS the
+                                 packs must also fit the register-resident adjoint kernel) */
+    int32_t cells_per_pack;   /* most cells one workgroup advances; 0 = the library's choice */
     int32_t dry_run_ranks;    /* dry-run mode (Sec. V-E): 0 or 1 = off; R > 1: the model's cells
                                  are rank 0 of R identical ranks, connection sources may be any
                                  gid in [0, R n_cells), and the spikes of gid g on another rank

@@ -69,15 +69,16 @@ struct PackDesc {
 // then its distal V; its contribution with no children, then its distal V
 // for a grounded parent; in packs of at most binary branch points, F_0 Q_0),
 // the conductance sum of each nonlinear CV (syn_sum), each generated
-// instance's current (ngen), the nonlinear entries, the children's tasks (other packs) and the slot of
-// each hh instance.
+// instance's current (ngen), the nonlinear entries, the children's tasks
+// (other packs) and the slot of each hh instance.
 
 // Packs with at most this many hh instances give each gate its own thread
 // in the register-resident kernel.
 constexpr int kSpreadHH = 20;
 
 // A register-resident pack whose synapses would take more LDS than this
-// keeps their state in HBM and streams it every step.  A pack of one cell
+// keeps their state in HBM and streams it, every step or (syn_sum) once a
+// launch.  A pack of one cell
 // too large for LDS otherwise reads its hh conductances and the step-invariant
 // right-hand side of its nonlinear CVs from HBM each step (hh_global).
 constexpr int64_t kSynLdsMax = 16384;
@@ -89,8 +90,8 @@ constexpr int64_t kSynLdsMax = 16384;
 // scales the conductances by the launch's decay once at its end: three passes
 // over them in all, against two a step streaming them (240 cells of 10,000
 // synapses, us a launch of 1, 2 and 3 steps: streaming 30, 45, 59; with sums
-// 36, 38, 40).  A single step streams.  Events enter a conductance divided by the decay since the launch's
-// start, kept above e^-kSumMaxLog.
+// 36, 38, 40).  A single step streams.  Events enter a conductance divided by
+// the decay since the launch's start, kept above e^-kSumMaxLog.
 constexpr int kSumMinSteps = 2;
 constexpr double kSumMaxLog = 300.0;
 

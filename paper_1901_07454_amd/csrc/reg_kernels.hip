@@ -133,8 +133,10 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
     };
 
     const bool rec = REC && a.rec_V != nullptr;
-    // a thread's hh CVs two at a time: in workgroups that hold large cells
-    constexpr bool PAIRS = !REC && !M && (T == 512 || (T == 256 && (S == 3 || (S == 1 && !G))));
+    // a thread's hh CVs two at a time: in 512 threads, which hold large cells;
+    // in 256 it loses (us a step one at a time / two: 256 cells of 321 hh CVs
+    // 4.2 / 4.8, 1024 of 505 9.5 / 11.0, 4096 uneven cells 54.8 / 56.6)
+    constexpr bool PAIRS = !REC && !M && T == 512;
     for (int i = tid; i < ns; i += T) {
         const double v = a.V[pk.slot0 + i];
         sV[vix(i)] = v;
