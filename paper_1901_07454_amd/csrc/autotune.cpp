@@ -56,7 +56,7 @@ uint64_t shape_key(const ModelView& m, const DeviceLimits& d, const arb_params& 
     mix(uint64_t(d.n_cu));
     mix(uint64_t(d.lds_max));
     mix(uint64_t((p.flags & ARB_FLAG_GRADIENTS) ? 1 : 0));
-    mix(6);  // version of the candidate set and kernels
+    mix(7);  // version of the candidate set and kernels
     return h;
 }
 
@@ -215,6 +215,7 @@ arb_params autotune(const ModelView& m, const arb_params& p, const DeviceLimits&
         }
         const int fill256 = int(std::max<int64_t>(1, 256 / max_width));
         const std::vector<Candidate> cands = {
+            {3, 0, 0},  // the library's own shape, which may be 512 threads
             {3, 256, 0}, {3, 128, 0}, {3, 64, 0}, {3, 64, 1}, {3, 128, 1},
             {2, 256, fill256}, {2, 256, std::max(1, fill256 / 2)}, {2, 128, std::max(1, fill256 / 2)},
             {2, 64, 1}, {1, 64, 1}, {1, 256, 0}};
