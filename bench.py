@@ -529,7 +529,12 @@ def main():
     value = n_cv * steps / wall
     steps_per_launch = steps / max(nlaunch, 1)
     avg_launch_s = kms / 1e3 / max(nlaunch, 1)
-    flops_per_step = FLOPS_PER_CV * n_cv + FLOPS_PER_HH * info["n_hh"] + FLOPS_PER_SYN * info["n_syn"]
+    # synapses held in HBM that share reversal potential and decay: a step works
+    # on one conductance sum per CV with synapses (at most every CV)
+    summed = (24 * info["n_syn"] > 16384 * info["n_cells"] and steps_per_launch >= 2
+              and len(np.unique(m["syn_tau"])) == len(np.unique(m["syn_e"])) == 1)
+    n_syn_work = min(info["n_syn"], n_cv) if summed else info["n_syn"]
+    flops_per_step = FLOPS_PER_CV * n_cv + FLOPS_PER_HH * info["n_hh"] + FLOPS_PER_SYN * n_syn_work
     gen_instances = {}
     if args.mech:  # each generated instance's operations, counted from its description
         from paper_1901_07454_amd import mechgen
@@ -549,7 +554,7 @@ def main():
     # the CV-dominated workloads its measured HBM traffic is a small fraction
     # of the peak and FP64 issue is the nearer roofline (the kernel itself is
     # bound by the latency of the solve's dependency chains); synapse-heavy
-    # workloads stream their synapse state and sit on HBM.
+    # workloads that stream their synapse state every step sit on HBM.
     alu_frac = tflops / FP64_PEAK_TFLOPS
     hbm_frac = None if traffic_gbps is None else traffic_gbps / HBM_PEAK_GBPS
     if hbm_frac is not None and hbm_frac > alu_frac:
@@ -563,7 +568,7 @@ def main():
         roof = {"bound": "alu", "achieved": tflops, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": alu_frac, "traffic": traffic,
                 "basis": ("algorithmic FP64 operations per launch (7 per CV, 61 per hh instance, 4 per "
-                          "synapse" + (", each generated mechanism instance the count of its description"
+                          + ("CV's sum of synapses" if summed else "synapse") + (", each generated mechanism instance the count of its description"
                                        if args.mech else "") +
                           ", per step taken) / average launch time; peak = MI355X vector FP64")}
     roof.update({
