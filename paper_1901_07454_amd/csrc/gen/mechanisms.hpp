@@ -6,31 +6,17 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
-#include "../fastexp.hpp"
 #include "mechanisms_desc.hpp"
 
 namespace arbmi {
 namespace gen {
 
-// e^x and e^x - 1 of any x from exp_pair (within 2 ulp; |x| < 700 there):
-// beyond it both saturate as the exact values do, and NaN stays NaN
-__device__ __forceinline__ ExpPair gen_exp_pair(double x) {
-    x = x > 720.0 ? 720.0 : x;
-    x = x < -750.0 ? -750.0 : x;
-    return exp_pair(x);
-}
-__device__ __forceinline__ double gen_exp(double x) { return gen_exp_pair(x).e; }
-__device__ __forceinline__ double gen_exprelr(double x) {  // free of branches
-    const double em1 = gen_exp_pair(x).em1;
+// x / (e^x - 1), 1 where 1 + x == 1 (its limit at 0); free of branches, so that
+// two instances overlap
+__device__ __forceinline__ double gen_exprelr(double x) {
+    const double em1 = expm1(x);
     const bool one = 1.0 + x == 1.0;
     return (one ? 1.0 : x) / (one ? 1.0 : em1);
-}
-// x / c for a constant c: the product with its reciprocal, corrected by the
-// exact remainder (the rounded quotient, but for a last bit now and then;
-// infinities pass)
-__device__ __forceinline__ double gen_div(double x, double c) {
-    const double r = 1.0 / c, q = x * r, e = fma(-q, c, x);
-    return e == e ? fma(e, r, q) : q;
 }
 
 // states of mechanism `id`
@@ -48,10 +34,10 @@ __device__ __forceinline__ double current0(double v, const double* prm, const do
 // hcn
 __device__ __forceinline__ void advance0(double v, double dt, const double* prm, double* st) {
     const double vhalf = prm[2];
-    const double qinf = (1.0 / (1.0 + gen_exp(gen_div((v - vhalf), 6.0))));
-    const double qtau = (50.0 + (200.0 / (1.0 + gen_exp(gen_div((v + 60.0), 10.0)))));
+    const double qinf = (1.0 / (1.0 + exp(((v - vhalf) / 6.0))));
+    const double qtau = (50.0 + (200.0 / (1.0 + exp(((v + 60.0) / 10.0)))));
     { const double xinf = qinf, xtau = qtau;
-      st[0] = xinf + (st[0] - xinf) * gen_exp(-dt / xtau); }
+      st[0] = xinf + (st[0] - xinf) * exp(-dt / xtau); }
 }
 // hh_dsl
 __device__ __forceinline__ double current1(double v, const double* prm, const double* st) {
@@ -69,17 +55,17 @@ __device__ __forceinline__ double current1(double v, const double* prm, const do
 // hh_dsl
 __device__ __forceinline__ void advance1(double v, double dt, const double* prm, double* st) {
     const double am = gen_exprelr(((-(v + 40.0)) * 0.1));
-    const double bm = (4.0 * gen_exp(((-(v + 65.0)) * (1.0 / 18.0))));
-    const double ah = (0.07 * gen_exp(((-(v + 65.0)) * 0.05)));
-    const double bh = (1.0 / (gen_exp(((-(v + 35.0)) * 0.1)) + 1.0));
+    const double bm = (4.0 * exp(((-(v + 65.0)) * (1.0 / 18.0))));
+    const double ah = (0.07 * exp(((-(v + 65.0)) * 0.05)));
+    const double bh = (1.0 / (exp(((-(v + 35.0)) * 0.1)) + 1.0));
     const double an = (0.1 * gen_exprelr(((-(v + 55.0)) * 0.1)));
-    const double bn = (0.125 * gen_exp(((-(v + 65.0)) * (1.0 / 80.0))));
+    const double bn = (0.125 * exp(((-(v + 65.0)) * (1.0 / 80.0))));
     { const double ra = am, rb = bm, rs = ra + rb, xinf = ra / rs;
-      st[0] = xinf + (st[0] - xinf) * gen_exp(-dt * rs); }
+      st[0] = xinf + (st[0] - xinf) * exp(-dt * rs); }
     { const double ra = ah, rb = bh, rs = ra + rb, xinf = ra / rs;
-      st[1] = xinf + (st[1] - xinf) * gen_exp(-dt * rs); }
+      st[1] = xinf + (st[1] - xinf) * exp(-dt * rs); }
     { const double ra = an, rb = bn, rs = ra + rb, xinf = ra / rs;
-      st[2] = xinf + (st[2] - xinf) * gen_exp(-dt * rs); }
+      st[2] = xinf + (st[2] - xinf) * exp(-dt * rs); }
 }
 // kdr
 __device__ __forceinline__ double current2(double v, const double* prm, const double* st) {
@@ -90,10 +76,10 @@ __device__ __forceinline__ double current2(double v, const double* prm, const do
 }
 // kdr
 __device__ __forceinline__ void advance2(double v, double dt, const double* prm, double* st) {
-    const double an = (0.16 * gen_exprelr(gen_div((-(v + 52.0)), 5.0)));
-    const double bn = (0.5 * gen_exp(gen_div((-(v + 57.0)), 40.0)));
+    const double an = (0.16 * gen_exprelr(((-(v + 52.0)) / 5.0)));
+    const double bn = (0.5 * exp(((-(v + 57.0)) / 40.0)));
     { const double ra = an, rb = bn, rs = ra + rb, xinf = ra / rs;
-      st[0] = xinf + (st[0] - xinf) * gen_exp(-dt * rs); }
+      st[0] = xinf + (st[0] - xinf) * exp(-dt * rs); }
 }
 
 // two instances of mechanism `id` at voltages v[0] and v[1]: their states st

@@ -173,26 +173,22 @@ def _num(x: float) -> str:
     return s if ("." in s or "e" in s or "inf" in s or "nan" in s) else s + ".0"
 
 
-def emit_expr(e, device: bool = False) -> str:
+def emit_expr(e) -> str:
     """C++ for an expression: every operation parenthesised, so the C++
-    evaluates exactly the tree that was written.  Device code calls gen_exp
-    for exp and gen_div for a division by a constant (render_device)."""
+    evaluates exactly the tree that was written."""
     k = e[0]
     if k == "num":
         return _num(e[1])
     if k == "var":
         return e[1]
     if k == "neg":
-        return f"(-{emit_expr(e[1], device)})"
+        return f"(-{emit_expr(e[1])})"
     if k == "call":
-        name = "gen_exprelr" if e[1] == "exprelr" else "gen_exp" if device and e[1] == "exp" else e[1]
-        return f"{name}({emit_expr(e[2], device)})"
+        return f"{'gen_exprelr' if e[1] == 'exprelr' else e[1]}({emit_expr(e[2])})"
     if k == "pow":
-        b = emit_expr(e[1], device)
+        b = emit_expr(e[1])
         return "(" + " * ".join([b] * e[2]) + ")"
-    if device and e[1] == "/" and e[3][0] == "num" and _names(e[2]) and 1e-3 <= e[3][1] <= 1e3:
-        return f"gen_div({emit_expr(e[2], device)}, {emit_expr(e[3])})"
-    return f"({emit_expr(e[2], device)} {e[1]} {emit_expr(e[3], device)})"
+    return f"({emit_expr(e[2])} {e[1]} {emit_expr(e[3])})"
 
 
 # ------------------------------------------------------------------ mechanisms
@@ -318,20 +314,19 @@ def _st(i: int) -> str:
     return f"st[{i}]"
 
 
-def _gate_lines(m: Mechanism, target: str, device: bool = False) -> list[str]:
+def _gate_lines(m: Mechanism, target: str) -> list[str]:
     """State updates (target 'advance') or steady states ('steady')."""
     out = []
     for g in m.gates:
         x = _st(m.states.index(g.state))
-        a, b = emit_expr(g.a, device), emit_expr(g.b, device)
-        exp = "gen_exp" if device else "exp"
+        a, b = emit_expr(g.a), emit_expr(g.b)
         if g.kind == "alpha_beta":
             out.append(f"{{ const double ra = {a}, rb = {b}, rs = ra + rb, xinf = ra / rs;")
-            out.append(f"  {x} = xinf + ({x} - xinf) * {exp}(-dt * rs); }}" if target == "advance"
+            out.append(f"  {x} = xinf + ({x} - xinf) * exp(-dt * rs); }}" if target == "advance"
                        else f"  {x} = xinf; }}")
         elif target == "advance":
             out.append(f"{{ const double xinf = {a}, xtau = {b};")
-            out.append(f"  {x} = xinf + ({x} - xinf) * {exp}(-dt / xtau); }}")
+            out.append(f"  {x} = xinf + ({x} - xinf) * exp(-dt / xtau); }}")
         else:
             out.append(f"{x} = {a};")
     return out
@@ -382,7 +377,7 @@ def op_count(m: Mechanism) -> int:
     return current + advance + sum(7 if g.kind == "alpha_beta" else 5 for g in m.gates)
 
 
-def _body(m: Mechanism, kind: str, device: bool = False) -> list[str]:
+def _body(m: Mechanism, kind: str) -> list[str]:
     if kind == "current":
         exprs = [m.current]
     elif kind == "steady":
@@ -391,20 +386,20 @@ def _body(m: Mechanism, kind: str, device: bool = False) -> list[str]:
         exprs = [g.a for g in m.gates] + [g.b for g in m.gates]
     need = _used(m, exprs)
     lines = [f"const double {p} = prm[{i}];" for i, (p, _) in enumerate(m.params) if p in need]
-    lines += [f"const double {r} = {emit_expr(e, device)};" for r, e in m.rates if r in need]
+    lines += [f"const double {r} = {emit_expr(e)};" for r, e in m.rates if r in need]
     if kind == "current":
         lines += [f"const double {s} = {_st(i)};" for i, s in enumerate(m.states) if s in need]
-        lines.append(f"return {emit_expr(m.current, device)};")
+        lines.append(f"return {emit_expr(m.current)};")
     else:
-        lines += _gate_lines(m, kind, device)
+        lines += _gate_lines(m, kind)
     return lines
 
 
-def _switch(cat: list[Mechanism], kind: str, indent: str, device: bool = False) -> str:
+def _switch(cat: list[Mechanism], kind: str, indent: str) -> str:
     out = []
     for k, m in enumerate(cat):
         out.append(f"{indent}case {k}: {{  // {m.name}")
-        out += [indent + "    " + ln for ln in _body(m, kind, device)]
+        out += [indent + "    " + ln for ln in _body(m, kind)]
         if kind != "current":
             out.append(indent + "    return;")
         out.append(indent + "}")
@@ -487,7 +482,7 @@ def _functions(cat: list[Mechanism]) -> str:
         for kind, head in (("current", f"double current{k}(double v, const double* prm, const double* st)"),
                            ("advance", f"void advance{k}(double v, double dt, const double* prm, double* st)")):
             out.append(f"// {m.name}\n__device__ __forceinline__ {head} {{")
-            out += ["    " + ln for ln in _body(m, kind, True)]
+            out += ["    " + ln for ln in _body(m, kind)]
             out.append("}")
     return "\n".join(out) + "\n"
 
@@ -523,31 +518,17 @@ def render_device(cat: list[Mechanism]) -> str:
 #pragma once
 #include <hip/hip_runtime.h>
 
-#include "../fastexp.hpp"
 #include "mechanisms_desc.hpp"
 
 namespace arbmi {{
 namespace gen {{
 
-// e^x and e^x - 1 of any x from exp_pair (within 2 ulp; |x| < 700 there):
-// beyond it both saturate as the exact values do, and NaN stays NaN
-__device__ __forceinline__ ExpPair gen_exp_pair(double x) {{
-    x = x > 720.0 ? 720.0 : x;
-    x = x < -750.0 ? -750.0 : x;
-    return exp_pair(x);
-}}
-__device__ __forceinline__ double gen_exp(double x) {{ return gen_exp_pair(x).e; }}
-__device__ __forceinline__ double gen_exprelr(double x) {{  // free of branches
-    const double em1 = gen_exp_pair(x).em1;
+// x / (e^x - 1), 1 where 1 + x == 1 (its limit at 0); free of branches, so that
+// two instances overlap
+__device__ __forceinline__ double gen_exprelr(double x) {{
+    const double em1 = expm1(x);
     const bool one = 1.0 + x == 1.0;
     return (one ? 1.0 : x) / (one ? 1.0 : em1);
-}}
-// x / c for a constant c: the product with its reciprocal, corrected by the
-// exact remainder (the rounded quotient, but for a last bit now and then;
-// infinities pass)
-__device__ __forceinline__ double gen_div(double x, double c) {{
-    const double r = 1.0 / c, q = x * r, e = fma(-q, c, x);
-    return e == e ? fma(e, r, q) : q;
 }}
 
 // states of mechanism `id`
