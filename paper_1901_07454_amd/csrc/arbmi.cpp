@@ -634,6 +634,11 @@ static int lower_planned(const ModelView& m, const arb_params& p, const Plan& pl
     };
     opt.grads = opt.grads || plan.long_cut;
     int rc = lower();
+    if (rc == ARB_OK && L.coef_mode == 3 &&
+        !has_reg_step(L.block_threads, L.reg_slots, L.reg_len, opt.grads && !plan.long_cut, !L.gen_mech.empty())) {
+        err = "no register-resident kernel for a cell of this model";
+        rc = ARB_EINVAL;
+    }
     long_cut = plan.long_cut && rc == ARB_OK;
     const bool auto_mode = p.coef_mode == 0 || (p.flags & ARB_FLAG_AUTOTUNE);
     if (rc == ARB_EINVAL && auto_mode && opt.coef_mode != 2 &&

@@ -139,6 +139,15 @@ inline int64_t reg_adjoint_lds_bytes(const PackDesc& D) {
     return 8 * dbl + 16 * int64_t(D.nnl) + (D.binary ? 0 : 4 * int64_t(D.nch)) + 4 * int64_t(D.nhh);
 }
 
+// The register-resident step kernels there are: branches of `len` CVs, `slots` of
+// them per thread; 512 threads take 8-CV branches, no recording (gradients), and
+// one slot with generated mechanisms.
+constexpr bool has_reg_step(int threads, int slots, int len, bool rec, bool gen) {
+    if (slots < 1 || slots > 3 || (len != 8 && len != 16) || (len == 16 && slots > 1)) return false;
+    if (threads == 512) return len == 8 && !rec && slots <= (gen ? 1 : 2);
+    return threads == 64 || threads == 128 || threads == 256;
+}
+
 struct RoundDesc {
     int32_t slot0;  // pack-local slot of (k = 0, first thread)
     int32_t w;      // branches in the round
