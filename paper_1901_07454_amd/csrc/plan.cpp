@@ -71,9 +71,11 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
     // 16.4 us a step streamed, 2.3 cut into segments; 8192 of them 22.5 / 5.5,
     // with every CV hh 75 / 31; one cell of a 2000-CV cable 363 / 26).  Up to
     // the segments that 256 threads hold, whose packs fit the adjoint's LDS
-    // (lower_planned).  arb_get_info still says coef_mode 2 for them.
+    // (lower_planned).  Models with generated mechanisms, which have no
+    // gradients, get it on request only.  arb_get_info still says coef_mode 2
+    // for them.
     pl.long_cut = p.coef_mode == 0 && max_len > 16 && p.block_threads == 0 && p.cells_per_pack == 0 && !grads &&
-                  !(p.flags & ARB_FLAG_AUTOTUNE) && max_tasks8 <= 768;
+                  !(p.flags & ARB_FLAG_AUTOTUNE) && p.n_densities == 0 && max_tasks8 <= 768;
     const bool reg_ok = p.coef_mode == 3 || (p.coef_mode == 0 && max_len <= 16) || pl.long_cut;
     if (reg_ok) {
         pl.coef_mode = 3;
@@ -119,7 +121,9 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
             // where the caller asked for this layout no more of them than it
             // takes with any other workgroup (an explicit request is honoured
             // or refused).
-            if (T == 256 && pl.reg_len == 8 && tasks > 256 && tasks <= (p.coef_mode == 3 ? 768 : 1024) && !grads && !pl.long_cut && p.n_densities == 0) T = 512;
+            if (T == 256 && pl.reg_len == 8 && tasks > 256 && tasks <= (p.coef_mode == 3 ? 768 : 1024) &&
+                !grads && !pl.long_cut && p.n_densities == 0)
+                T = 512;
             // Cells with generated mechanisms and more nonlinear CVs than 256
             // threads, where each has a CU to itself (by number, or by LDS):
             // a step is mostly visits of their instances, in series per

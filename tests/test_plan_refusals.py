@@ -1,5 +1,7 @@
 """Layouts that are asked for and cannot be had are refused, with the reason
 (CPU: plans only)."""
+import ctypes as C
+
 import pytest
 
 from paper_1901_07454_amd import arbmi
@@ -20,3 +22,15 @@ def test_register_layout_asked_for_takes_768_branches(branches, fits):
             with pytest.raises(arbmi.ArbError, match="register"):
                 _plan(m, coef_mode=3, **kw)
     assert _plan(m)["coef_mode"] == 3
+
+
+def test_generated_mechanisms_on_long_branches():
+    """Branches of more than 16 CVs with generated mechanisms: the plan is
+    refused with what to ask for, and what was asked for is planned."""
+    m = gen.assemble(_cells(1, 40, 24), n_steps=10)
+    dens = arbmi.density_structs([(0, b, "kdr", {}) for b in range(40)])
+    kw = {"densities": C.cast(dens, C.c_void_p), "n_densities": len(dens)}
+    with pytest.raises(arbmi.ArbError, match="coef_mode 3"):
+        _plan(m, **kw)
+    info = _plan(m, coef_mode=3, **kw)
+    assert info["coef_mode"] == 3 and info["reg_len"] == 8 and info["reg_slots"] > 0
