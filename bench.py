@@ -531,7 +531,7 @@ def main():
     avg_launch_s = kms / 1e3 / max(nlaunch, 1)
     # synapses held in HBM that share reversal potential and decay: a step works
     # on one conductance sum per CV with synapses (at most every CV)
-    summed = (24 * info["n_syn"] > 16384 * info["n_cells"] and steps_per_launch >= 2
+    summed = (24 * info["n_syn"] > 16384 * info["n_cells"]
               and len(np.unique(m["syn_tau"])) == len(np.unique(m["syn_e"])) == 1)
     n_syn_work = min(info["n_syn"], n_cv) if summed else info["n_syn"]
     flops_per_step = FLOPS_PER_CV * n_cv + FLOPS_PER_HH * info["n_hh"] + FLOPS_PER_SYN * n_syn_work

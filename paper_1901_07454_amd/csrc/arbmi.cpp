@@ -123,6 +123,7 @@ StepArgs Sim::step_args() const {
     a.hh_gna = d_hh_gna;
     a.hh_gk = d_hh_gk;
     a.syn_g = d_syn_g;
+    a.syn_sum = d_syn_sum;
     a.syn_e = d_syn_e;
     a.syn_decay = d_syn_decay;
     a.ic_slot = d_ic_slot;
@@ -519,6 +520,7 @@ int build_device(Sim* s) {
     s->d_hh_gk = dupload(s, L.hh_gk, rc);
     const size_t nsyn = L.syn_global.size();
     s->d_syn_g = dupload(s, std::vector<double>(nsyn, 0.0), rc);
+    if (L.n_sum) s->d_syn_sum = dupload(s, conductance_sums(L, std::vector<double>(nsyn, 0.0).data()), rc);
     s->d_syn_e = dupload(s, L.syn_e, rc);
     s->d_syn_decay = dupload(s, L.syn_decay, rc);
     s->d_ic_slot = dupload(s, L.ic_slot, rc);
@@ -1264,11 +1266,13 @@ int arb_get_state(arb_sim s_, void* blob, int64_t cap, int64_t* n_out) {
     s->state_part_ptrs(ptr);
     int64_t total = sizeof(StateHeader);
     for (int k = 0; k < kStateParts; ++k) total += bytes[k];
+    const int64_t sum_bytes = 8 * L.n_sum;  // after the parts
+    total += sum_bytes;
     *n_out = total;
     if (!blob) return ARB_OK;
     if (cap < total) return fail(ARB_EOVERFLOW, "state blob capacity too small");
     const int64_t np = int64_t(L.packs.size());
-    StateHeader h{sh.magic, s->step, L.n_slots, int64_t(L.hh_cv.size()), int64_t(L.syn_global.size()),
+    StateHeader h{L.n_sum ? sh.magic ^ kStateSums : sh.magic, s->step, L.n_slots, int64_t(L.hh_cv.size()), int64_t(L.syn_global.size()),
                   np, np, s->bk_cap, s->sp_cap, s->sp_user};
     char* out = static_cast<char*>(blob);
     std::memcpy(out, &h, sizeof h);
@@ -1277,6 +1281,7 @@ int arb_get_state(arb_sim s_, void* blob, int64_t cap, int64_t* n_out) {
         if (bytes[k]) HIP_TRY(hipMemcpyAsync(out + at, ptr[k], size_t(bytes[k]), hipMemcpyDeviceToHost, s->st));
         at += bytes[k];
     }
+    if (sum_bytes) HIP_TRY(hipMemcpyAsync(out + at, s->d_syn_sum, size_t(sum_bytes), hipMemcpyDeviceToHost, s->st));
     HIP_TRY(hipStreamSynchronize(s->st));
     return ARB_OK;
 }
@@ -1303,6 +1308,17 @@ int arb_set_state(arb_sim s_, const void* blob, int64_t n) {
     for (int k = 0; k < kStateParts; ++k) {
         if (bytes[k]) HIP_TRY(hipMemcpyAsync(ptr[k], in + at, size_t(bytes[k]), hipMemcpyHostToDevice, s->st));
         at += bytes[k];
+    }
+    std::vector<double> sums(size_t(L.n_sum), 0.0);
+    if (L.n_sum) {  // the blob's, or the sums of its conductances
+        if (h.magic == sh.magic) {
+            std::vector<double> g(size_t(bytes[4]) / 8);
+            std::memcpy(g.data(), in + sizeof h + bytes[0] + bytes[1] + bytes[2] + bytes[3], size_t(bytes[4]));
+            sums = conductance_sums(L, g.data());
+        } else {
+            std::memcpy(sums.data(), in + at, size_t(8 * L.n_sum));
+        }
+        HIP_TRY(hipMemcpyAsync(s->d_syn_sum, sums.data(), size_t(8 * L.n_sum), hipMemcpyHostToDevice, s->st));
     }
     HIP_TRY(hipStreamSynchronize(s->st));
     s->step = h.step;

@@ -32,6 +32,7 @@ struct StepArgs {
     const double* hh_gna;      // nS
     const double* hh_gk;
     double* syn_g;             // [n_syn] nS
+    double* syn_sum;           // conductance sums (PackDesc::sum0)
     const double* syn_e;
     const double* syn_decay;   // exp(-dt/tau)
     const int32_t* ic_slot;    // pack-local slot of each clamp

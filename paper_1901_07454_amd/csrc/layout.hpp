@@ -52,8 +52,10 @@ struct PackDesc {
                          // beta stay in HBM (a cell too large for LDS otherwise)
     int64_t xe0, xe1; // external events [xe0, xe1), sorted by (step, syn, input order)
     double syn_e, syn_decay;  // the shared values when syn_uniform
-    int32_t syn_sum; // syn_global packs that are syn_uniform: a launch keeps one conductance sum per
-                     // nonlinear CV in LDS (kSumMinSteps), if LDS has room for them
+    int64_t sum0;    // first entry of the pack's conductance sums (syn_sum): one per nonlinear CV, then
+                     // the decay since the conductances were last exact
+    int32_t syn_sum; // syn_global packs that are syn_uniform: one conductance sum per nonlinear CV
+                     // takes the conductances' place in a step (kSumMinDecay), if LDS has room
     int32_t ngen;    // generated-mechanism instances whose currents a launch keeps in LDS (0: in HBM)
 };
 
@@ -77,23 +79,24 @@ struct PackDesc {
 constexpr int kSpreadHH = 20;
 
 // A register-resident pack whose synapses would take more LDS than this
-// keeps their state in HBM and streams it, every step or (syn_sum) once a
-// launch.  A pack of one cell
-// too large for LDS otherwise reads its hh conductances and the step-invariant
+// keeps their state in HBM and streams it every step, or (syn_sum) carries
+// their sums.  A pack of one cell too large for LDS otherwise reads its hh conductances and the step-invariant
 // right-hand side of its nonlinear CVs from HBM each step (hh_global).
 constexpr int64_t kSynLdsMax = 16384;
 
 // A pack whose HBM synapses share reversal potential and decay (syn_sum)
 // needs only the sum of each CV's conductances in a step: the sums of decaying
-// terms with one rate decay at that rate.  A launch of at least kSumMinSteps
-// steps therefore reads the conductances once, carries the sums in LDS, and
-// scales the conductances by the launch's decay once at its end: three passes
-// over them in all, against two a step streaming them (240 cells of 10,000
-// synapses, us a launch of 1, 2 and 3 steps: streaming 30, 45, 59; with sums
-// 36, 38, 40).  A single step streams.  Events enter a conductance divided by
-// the decay since the launch's start, kept above e^-kSumMaxLog.
-constexpr int kSumMinSteps = 2;
-constexpr double kSumMaxLog = 300.0;
+// terms with one rate decay at that rate.  The sums are state, like the
+// conductances: kept from launch to launch, in LDS during one, so that a run's
+// results do not depend on how its steps are split into launches.  The
+// conductances in HBM wait, as of an earlier step: the pack's `since` is the
+// decay from then to now, an event enters a conductance divided by it, and
+// once it falls below kSumMinSince (after a number of steps that depends on
+// the decay alone) the conductances are scaled by it, one pass over them.
+// With a faster decay than kSumMinDecay, whose passes would come more often
+// than every 90 steps or so, a pack streams.
+constexpr double kSumMinDecay = 0.35;
+constexpr double kSumMinSince = 1e-40;
 
 // Incoming connections a pack of several cells may have: one workgroup
 // pulls and delivers all of its pack's network events.

@@ -867,9 +867,13 @@ int lower_model(const arb_cell* cells, int32_t n_cells, const arb_branch* br, in
         D.nic = int32_t(L.ic_on.size()) - D.ic0;
         D.nhh = int32_t(L.hh_cv.size()) - D.hh0;
         D.nsyn = int32_t(L.syn_global.size()) - D.syn0;
-        if (D.syn_global && D.syn_uniform && D.syn_decay > 0.0) {
+        if (D.syn_global && D.syn_uniform && D.syn_decay >= kSumMinDecay) {
             D.syn_sum = 1;
             if (pack_lds_bytes(D, L.coef_mode) > opt.lds_hard_max) D.syn_sum = 0;
+        }
+        if (D.syn_sum) {
+            D.sum0 = L.n_sum;
+            L.n_sum += int64_t(D.nnl) + 1;
         }
         if (n_den > 0 && (D.syn_global || D.hh_global) && L.gen_pk.back() != int32_t(L.gen_mech.size())) {
             err = "generated mechanisms do not run on a cell whose state is held in HBM (too large for LDS)";
@@ -1116,6 +1120,23 @@ std::string verify_layout(const Lowered& L) {
     return "";
 }
 
+// The conductance sums of packs whose conductances g are exact (since = 1).
+std::vector<double> conductance_sums(const Lowered& L, const double* g) {
+    std::vector<double> out(size_t(L.n_sum), 0.0);
+    for (const PackDesc& D : L.packs) {
+        if (!D.syn_sum) continue;
+        for (int32_t j = 0; j < D.nnl; ++j) {
+            const NlDesc& N = L.nl[size_t(D.nl0) + size_t(j)];
+            const int32_t w = std::min(L.block_threads, D.nnl - (j / L.block_threads) * L.block_threads);
+            double s = 0.0;
+            for (int64_t k = 0; k < N.nsyn; ++k) s += g[D.syn0 + N.syn0 + k * w];
+            out[size_t(D.sum0 + j)] = s;
+        }
+        out[size_t(D.sum0 + D.nnl)] = 1.0;
+    }
+    return out;
+}
+
 // alpha_i = c_i/dt - G_lin,i and beta_i = sum G e over the linear terms
 // (pas and the hh leak), so that the right-hand side of the implicit-Euler
 // system is  rhs_i = alpha_i V_i + beta_i - (nonlinear and point currents).
@@ -1161,15 +1182,22 @@ std::string check_state_blob(const Lowered& L, const StateShape& sh, const void*
     std::memcpy(&h, blob, sizeof h);
     const int64_t np = int64_t(L.packs.size());
     const int64_t nhh = int64_t(L.hh_cv.size()), nsyn = int64_t(L.syn_global.size());
-    if (h.magic != sh.magic || h.n_slots != L.n_slots || h.n_hh != nhh || h.n_syn != nsyn || h.n_packs != np ||
+    const bool sums = L.n_sum > 0 && h.magic == (sh.magic ^ kStateSums);
+    if ((!sums && h.magic != sh.magic) || h.n_slots != L.n_slots || h.n_hh != nhh || h.n_syn != nsyn || h.n_packs != np ||
         h.n_bk != np || h.bk_cap != sh.bk_cap || h.sp_cap != int64_t(sh.sp_cap))
         return "state blob does not belong to this model";
     int64_t bytes[kStateParts];
     state_part_bytes(L, sh, bytes);
     int64_t total = sizeof(StateHeader);
     for (int k = 0; k < kStateParts; ++k) total += bytes[k];
-    if (n < total) return "state blob truncated";
+    if (n < total + (sums ? 8 * L.n_sum : 0)) return "state blob truncated";
     const char* in = static_cast<const char*>(blob);
+    for (const PackDesc& D : L.packs) {
+        if (!sums || !D.syn_sum) continue;
+        double since;
+        std::memcpy(&since, in + total + 8 * (D.sum0 + D.nnl), 8);
+        if (!(since > 0.0 && since <= 1.0)) return "state blob: decay since the conductances out of range";
+    }
     const char* part[kStateParts];
     int64_t off = sizeof h;
     for (int k = 0; k < kStateParts; ++k) {

@@ -102,6 +102,7 @@ struct Lowered {
     int32_t min_delay = 0, max_delay = 0;
     int64_t max_in_per_pack = 0;              // incoming connections of the busiest pack
     int64_t n_hh_total = 0;
+    int64_t n_sum = 0;                        // conductance sums of every pack (PackDesc::sum0)
 };
 
 struct LowerOptions {
@@ -153,6 +154,12 @@ struct StateHeader {
 };
 
 constexpr int kStateParts = 18;
+// A sim with conductance sums (PackDesc::syn_sum) writes kStateMagic ^ kStateSums
+// and the sums after the parts; without them (a blob of a build that streamed
+// the conductances, or summed them once a launch) the conductances are exact
+// and the sums follow from them.
+constexpr uint64_t kStateSums = uint64_t(64) << 56;
+std::vector<double> conductance_sums(const Lowered& L, const double* g);
 // Bytes of each part.
 void state_part_bytes(const Lowered& L, const StateShape& sh, int64_t bytes[kStateParts]);
 // Every check arb_set_state makes before any byte reaches the device: the

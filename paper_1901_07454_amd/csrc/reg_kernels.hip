@@ -115,16 +115,15 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
     int32_t* s_hhs = s_ch + (pk.binary ? 0 : pk.nch);          // per hh instance: its CV's slot
     int32_t* s_goff = s_hhs + pk.nhh;                          // each entry's first instance (ngen)
 
-    // One conductance sum per nonlinear CV for the launch (kSumMinSteps in
-    // layout.hpp), instead of streaming every conductance each step, which
+    // One conductance sum per nonlinear CV (kSumMinDecay in layout.hpp),
+    // instead of streaming every conductance each step, which
     // took 15,500 of 19,800 cycles a step (10,000 synapses a cell: 77 read and
     // written in series by each of the 130 threads that have a CV; at 8192
     // cells, the whole HBM rate).  Only events then touch HBM during a step.
     // 240 cells x 10,000 synapses, all connected: 13.6 us a step streaming,
     // 3.5 with the sums.
-    const bool sums = G && syn_hbm && pk.syn_sum && a.nsteps >= kSumMinSteps &&
-                      a.nsteps * -log(pk.syn_decay) <= kSumMaxLog;
-    double since = 1.0;  // the decay since the launch's start
+    const bool sums = G && pk.syn_sum;
+    double since = sums ? a.syn_sum[pk.sum0 + pk.nnl] : 1.0;  // the decay since the conductances were exact
     // the nonlinear entry of a synapse (groups of T entries, interleaved)
     auto entry_of = [&](int q) {
         int u0 = 0;
@@ -171,6 +170,7 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
         s_nl[i] = d;
         if (!hh_hbm) s_nlb[i] = a.beta[pk.slot0 + d.slot];
         if (d.hh >= 0) s_hhs[d.hh] = vix(d.slot);
+        if (sums) s_sum[i] = a.syn_sum[pk.sum0 + i];
     }
     if (!pk.binary)
         for (int i = tid; i < pk.nch; i += T) s_ch[i] = a.ch_task[pk.ch0 + i];
@@ -307,22 +307,6 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
     }
     // the V entry of this thread's gate in the spread update, fixed for the launch
     const int hv = (pk.nhh <= kSpreadHH && tid < 3 * pk.nhh) ? s_hhs[hq] : 0;
-    if (sums) {
-        for (int j = tid; j < pk.nnl; j += T) {
-            const NlDesc d = s_nl[j];
-            const int w = min(T, pk.nnl - (j / T) * T);
-            double s = 0.0;
-            for (int k0 = 0; k0 < d.nsyn; k0 += 8) {  // eight loads in flight
-                double gg[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) gg[i] = g_g[d.syn0 + min(k0 + i, d.nsyn - 1) * w];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) s += (k0 + i < d.nsyn) ? gg[i] : 0.0;
-            }
-            s_sum[j] = s;
-        }
-        __syncthreads();
-    }
 
     for (int s = 0; s < a.nsteps; ++s) {
         const int64_t n = step0 + s;
@@ -699,15 +683,22 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
             }
             if (!pk.ngen) __threadfence_block();  // before the next step's sums read them
         }
-        if (sums)
+        if (sums) {
             since *= pk.syn_decay;
-        else if (syn_hbm)
+            if (since < kSumMinSince) {  // every event's store came before its step's fence and barrier
+                for (int i = tid; i < pk.nsyn; i += T) g_g[i] *= since;
+                since = 1.0;
+                __threadfence_block();
+            }
+        } else if (syn_hbm) {
             __threadfence_block();  // phase B's g stores before the next step's events
+        }
         round_sync<T>();
     }
 
-    if (sums) {  // every event's store is ordered before this by its step's fence and barrier
-        for (int i = tid; i < pk.nsyn; i += T) g_g[i] *= since;
+    if (sums) {
+        for (int i = tid; i < pk.nnl; i += T) a.syn_sum[pk.sum0 + i] = s_sum[i];
+        if (tid == 0) a.syn_sum[pk.sum0 + pk.nnl] = since;
     }
     for (int i = tid; i < ns; i += T) a.V[pk.slot0 + i] = sV[vix(i)];
     for (int i = tid; i < nsyn_lds; i += T) g_g[i] = sg[i];
