@@ -492,8 +492,8 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
                     h[u] = sh[q];
                     x[u] = sn[q];
                     bnl[u] = hh_hbm ? a.beta[pk.slot0 + d[u].slot] : s_nlb[u ? j2 : j];
-                    gna[u] = hh_hbm ? a.hh_gna[pk.hh0 + q] : s_gna[q];
-                    gk[u] = hh_hbm ? a.hh_gk[pk.hh0 + q] : s_gk[q];
+                    gna[u] = hh_hbm ? (d[u].hh >= 0 ? a.hh_gna[pk.hh0 + q] : 0.0) : s_gna[q];
+                    gk[u] = hh_hbm ? (d[u].hh >= 0 ? a.hh_gk[pk.hh0 + q] : 0.0) : s_gk[q];
                 }
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
