@@ -200,6 +200,7 @@ int Sim::launch_classes(const StepArgs& a0) {
         LaunchCfg lc = cfg;
         lc.lds_bytes = classes[c].lds;
         lc.syn_hbm = classes[c].hbm;
+        lc.syn_sum = classes[c].sum;
         if (cfg.coef_mode == 3) lc.reg_slots = classes[c].slots;
         hipStream_t s_c = (classes[c].stream == 0) ? st : aux[classes[c].stream - 1];
         if (timed)
@@ -730,6 +731,7 @@ int build_sim(const ModelView& m, const arb_params& pp, const DeviceLimits& d, S
     s->cfg.reg_slots = s->L.reg_slots;
     s->cfg.reg_len = s->L.reg_len;
     s->cfg.syn_hbm = 0;
+    s->cfg.syn_sum = s->L.n_sum ? 1 : 0;
     s->cfg.rec = (s->L.coef_mode == 3 && (p->flags & ARB_FLAG_GRADIENTS)) ? 1 : 0;
     s->cfg.gen = s->L.gen_mech.empty() ? 0 : 1;
     int64_t lds = 0;
@@ -776,15 +778,20 @@ int build_sim(const ModelView& m, const arb_params& pp, const DeviceLimits& d, S
         int32_t start = 0;
         Key cur = np ? key_of(0) : Key{0, 0, 0};
         int64_t mx = 0;
+        int sum = 0;
         for (int32_t k = 0; k <= np; ++k) {
             const bool end_run = (k == np) || !(key_of(k) == cur);
             if (end_run && k > start) {
-                s->classes.push_back({start, k - start, int(std::max<int64_t>(mx, 8)), cur.hbm, cur.slots, 0});
+                s->classes.push_back({start, k - start, int(std::max<int64_t>(mx, 8)), cur.hbm, sum, cur.slots, 0});
                 start = k;
                 mx = 0;
+                sum = 0;
                 if (k < np) cur = key_of(k);
             }
-            if (k < np) mx = std::max(mx, pack_lds_bytes(L.packs[k], L.coef_mode));
+            if (k < np) {
+                mx = std::max(mx, pack_lds_bytes(L.packs[k], L.coef_mode));
+                sum |= L.packs[k].syn_sum;
+            }
         }
         // a class of a few packs is not worth a stream of its own: merge it
         // into the previous class if that uses as many register slots (the
@@ -795,6 +802,7 @@ int build_sim(const ModelView& m, const arb_params& pp, const DeviceLimits& d, S
                 merged.back().npack += c.npack;
                 merged.back().lds = std::max(merged.back().lds, c.lds);
                 merged.back().hbm |= c.hbm;
+                merged.back().sum |= c.sum;
                 continue;
             }
             merged.push_back(c);

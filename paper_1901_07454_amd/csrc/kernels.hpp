@@ -32,7 +32,6 @@ struct StepArgs {
     const double* hh_gna;      // nS
     const double* hh_gk;
     double* syn_g;             // [n_syn] nS
-    double* syn_sum;           // conductance sums (PackDesc::sum0)
     const double* syn_e;
     const double* syn_decay;   // exp(-dt/tau)
     const int32_t* ic_slot;    // pack-local slot of each clamp
@@ -96,16 +95,18 @@ struct StepArgs {
     const double* gen_prm;     // [n_rows][kMaxParams]
     double* gen_st;            // [kMaxStates][n_inst], state-major
     int64_t gen_n;             // instances (the state-major stride)
+    double* syn_sum;           // conductance sums (PackDesc::sum0)
 };
 
 // Per-launch configuration chosen by the host.
 struct LaunchCfg {
-    int block_threads;  // 64, 128, 256
+    int block_threads;  // 64, 128, 256; 512 in mode 3
     int coef_mode;      // 1 LDS, 2 streamed, 3 register-resident
     int lds_bytes;      // dynamic LDS per workgroup
     int reg_slots;      // mode 3: branches per thread
     int reg_len;        // mode 3: CVs per branch held in registers (8 or 16)
     int syn_hbm;        // mode 3: some pack keeps its synapse state in HBM
+    int syn_sum;        // mode 3: some pack carries conductance sums (PackDesc::syn_sum)
     int rec;            // mode 3: the sim is built for gradients (kernels that can record states)
     int gen;            // mode 3: the model has generated density mechanisms
 };

@@ -52,11 +52,11 @@ struct PackDesc {
                          // beta stay in HBM (a cell too large for LDS otherwise)
     int64_t xe0, xe1; // external events [xe0, xe1), sorted by (step, syn, input order)
     double syn_e, syn_decay;  // the shared values when syn_uniform
-    int64_t sum0;    // first entry of the pack's conductance sums (syn_sum): one per nonlinear CV, then
-                     // the decay since the conductances were last exact
     int32_t syn_sum; // syn_global packs that are syn_uniform: one conductance sum per nonlinear CV
                      // takes the conductances' place in a step (kSumMinDecay), if LDS has room
     int32_t ngen;    // generated-mechanism instances whose currents a launch keeps in LDS (0: in HBM)
+    int64_t sum0;    // first entry of the pack's conductance sums (syn_sum): one per nonlinear CV, then
+                     // the decay since the conductances were last exact
 };
 
 // Bytes of dynamic LDS the step kernel uses for a pack.  Layout in the

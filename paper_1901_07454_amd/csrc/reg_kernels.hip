@@ -62,7 +62,8 @@ struct GenStates {
 // machine loop-invariant code motion): three for one slot of 8 CVs, two for
 // 16 CVs in all, one otherwise.  G: some pack of the launch keeps state in
 // HBM, its synapses' or its hh conductances' (without it, those paths are
-// compiled out).  REC: the
+// compiled out).  SUM (with G): some pack carries conductance sums (both
+// ways for synapse state in one kernel cost the others 5 to 7% of a step).  REC: the
 // sim is built for gradients; the steps record their states when a.rec_V
 // is set (the adjoint's recompute), and the gradient forward runs the same
 // code with it unset, so both produce the same trajectory bit for bit (one
@@ -70,7 +71,7 @@ struct GenStates {
 // the registers).  M: the model has generated density mechanisms (their
 // currents join the nonlinear CVs' right-hand sides, their states advance
 // with the gates; parameters and states stay in HBM).
-template <int T, int S, int L, bool G, bool REC, bool M = false>
+template <int T, int S, int L, bool G, bool REC, bool M = false, bool SUM = false>
 __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ? 2 : 1) : ((S * L <= 8) ? 3 : (S * L <= 16 ? 2 : 1)))
     reg_step_kernel(StepArgs a) {
     extern __shared__ __align__(16) char lds_raw[];
@@ -109,7 +110,7 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
     double* sY = sF;
     double* sQ = sF + (pk.ntk + 2);
     double* s_sum = sQ + (pk.binary ? pk.ntk + 2 : 0);         // conductance sums (syn_sum)
-    double* s_cur = s_sum + (G && pk.syn_sum ? pk.nnl : 0);    // generated instances' currents (ngen)
+    double* s_cur = s_sum + (SUM && pk.syn_sum ? pk.nnl : 0);    // generated instances' currents (ngen)
     NlDesc* s_nl = reinterpret_cast<NlDesc*>(s_cur + (M ? pk.ngen : 0));
     int32_t* s_ch = reinterpret_cast<int32_t*>(s_nl + pk.nnl);  // children's tasks (other packs)
     int32_t* s_hhs = s_ch + (pk.binary ? 0 : pk.nch);          // per hh instance: its CV's slot
@@ -122,7 +123,7 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
     // cells, the whole HBM rate).  Only events then touch HBM during a step.
     // 240 cells x 10,000 synapses, all connected: 13.6 us a step streaming,
     // 3.5 with the sums.
-    const bool sums = G && pk.syn_sum;
+    const bool sums = SUM && pk.syn_sum;
     double since = sums ? a.syn_sum[pk.sum0 + pk.nnl] : 1.0;  // the decay since the conductances were exact
     // the nonlinear entry of a synapse (groups of T entries, interleaved)
     auto entry_of = [&](int q) {
@@ -719,6 +720,9 @@ hipError_t launch_reg(const StepArgs& a, const LaunchCfg& cfg, int n_packs, hipS
     } else if (cfg.rec) {  // gradient sims never keep synapse state in HBM
         if (cfg.syn_hbm) return hipErrorInvalidValue;
         hipLaunchKernelGGL((reg_step_kernel<T, S, L, false, true>), dim3(n_packs), dim3(T), cfg.lds_bytes, st, a);
+    } else if (cfg.syn_sum) {
+        hipLaunchKernelGGL((reg_step_kernel<T, S, L, true, false, false, true>), dim3(n_packs), dim3(T), cfg.lds_bytes,
+                           st, a);
     } else if (cfg.syn_hbm) {
         hipLaunchKernelGGL((reg_step_kernel<T, S, L, true, false>), dim3(n_packs), dim3(T), cfg.lds_bytes, st, a);
     } else {
@@ -727,9 +731,9 @@ hipError_t launch_reg(const StepArgs& a, const LaunchCfg& cfg, int n_packs, hipS
     return hipGetLastError();
 }
 
-template <int T, int S, int L, bool G, bool REC, bool M = false>
+template <int T, int S, int L, bool G, bool REC, bool M = false, bool SUM = false>
 void allow_lds_one(int lds_max) {
-    const void* f = reinterpret_cast<const void*>(&reg_step_kernel<T, S, L, G, REC, M>);
+    const void* f = reinterpret_cast<const void*>(&reg_step_kernel<T, S, L, G, REC, M, SUM>);
     hipFuncAttributes at{};
     if (hipFuncGetAttributes(&at, f) != hipSuccess) return;
     const int allowed = lds_max - int(at.sharedSizeBytes);
@@ -741,6 +745,7 @@ template <int T, int S, int L>
 void allow_lds(int lds_max) {
     allow_lds_one<T, S, L, false, false>(lds_max);
     allow_lds_one<T, S, L, true, false>(lds_max);
+    allow_lds_one<T, S, L, true, false, false, true>(lds_max);
     allow_lds_one<T, S, L, false, true>(lds_max);
     allow_lds_one<T, S, L, false, false, true>(lds_max);
 }
@@ -751,6 +756,7 @@ template <int S>
 void allow_lds_512(int lds_max) {
     allow_lds_one<512, S, 8, false, false>(lds_max);
     allow_lds_one<512, S, 8, true, false>(lds_max);
+    allow_lds_one<512, S, 8, true, false, false, true>(lds_max);
     if constexpr (S == 1) allow_lds_one<512, S, 8, false, false, true>(lds_max);
 }
 template <int S>
@@ -760,7 +766,10 @@ hipError_t launch_reg_512(const StepArgs& a, const LaunchCfg& cfg, int n_packs, 
         if constexpr (S == 1)
             hipLaunchKernelGGL((reg_step_kernel<512, S, 8, false, false, true>), dim3(n_packs), dim3(512),
                                cfg.lds_bytes, st, a);
-    } else if (cfg.syn_hbm)
+    } else if (cfg.syn_sum)
+        hipLaunchKernelGGL((reg_step_kernel<512, S, 8, true, false, false, true>), dim3(n_packs), dim3(512),
+                           cfg.lds_bytes, st, a);
+    else if (cfg.syn_hbm)
         hipLaunchKernelGGL((reg_step_kernel<512, S, 8, true, false>), dim3(n_packs), dim3(512), cfg.lds_bytes, st, a);
     else
         hipLaunchKernelGGL((reg_step_kernel<512, S, 8, false, false>), dim3(n_packs), dim3(512), cfg.lds_bytes, st, a);

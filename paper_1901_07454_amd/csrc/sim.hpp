@@ -52,6 +52,7 @@ struct Sim : arb_sim_ {
     struct Class {
         int32_t pack0, npack, lds;
         int hbm;     // some pack of the class keeps state in HBM (the kernel variant that can)
+        int sum;     // some pack of the class carries conductance sums
         int slots;   // register slots its packs use (register layout), else 0
         int stream;  // 0: the sim's stream, k > 0: aux[k - 1]
     };

@@ -91,3 +91,32 @@ def test_512_threads_match_the_oracle(n_branch, uniform):
     sp = sim.spikes()
     assert sp["step"].tolist() == step.tolist() and sp["gid"].tolist() == gid.tolist()
     sim.close()
+
+
+@pytest.mark.parametrize("T", [64, 256])
+def test_both_kinds_in_one_launch(T):
+    """Cells that carry sums, cells that stream and a cell with its synapses
+    in LDS, in one launch class (the variant for sums), against the oracle."""
+    from paper_1901_07454_amd import arbmi
+    from tests import models
+    from workloads import gen
+    rng = np.random.default_rng(3)
+    cells = []
+    for n_syn, tau2 in ((800, 2.0), (800, 3.0), (20, 2.0), (900, 2.0)):
+        d = models.bare_cell([-1] + [(b - 1) // 2 for b in range(1, 40)], rng.integers(3, 9, 40),
+                             rng.uniform(100, 200, 40), rng.uniform(1, 3, 40))
+        br = rng.integers(40, size=n_syn - 1)
+        d.syn = [(-1, 0, 2.0, 0.0)] + [(int(b), int(rng.integers(d.n_cv[b])), 2.0, 0.0) for b in br]
+        d.syn[-1] = d.syn[-1][:2] + (tau2, 0.0)
+        d.ext = [(0, 3, 0.05)] + [(int(q), int(s), 1e-3) for q, s in zip(rng.integers(n_syn, size=200),
+                                                                         rng.integers(0, 200, 200))]
+        cells.append(d)
+    m = gen.assemble(cells, n_steps=200)
+    ref = oracle.Sim(m)
+    ref.run(200)
+    sim = arbmi.Simulation(m, block_threads=T, coef_mode=3, cells_per_pack=1)
+    assert sim.info["n_packs"] == 4 and sim.info["n_classes"] == 1
+    sim.step(200)
+    V = sim.voltages_host()
+    sim.close()
+    assert np.max(np.abs(V - ref.state()["V"])) <= TOL
