@@ -132,6 +132,9 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
         return u0 + (q - s_nl[u0].syn0) % min(T, pk.nnl - u0);
     };
 
+    // (with no hh instance, the address of a value that is there)
+    const double* g_gna = pk.nhh ? a.hh_gna + pk.hh0 : a.beta + pk.slot0;
+    const double* g_gk = pk.nhh ? a.hh_gk + pk.hh0 : a.beta + pk.slot0;
     const bool rec = REC && a.rec_V != nullptr;
     // a thread's hh CVs two at a time: in 512 threads, which hold large cells;
     // in 256 it loses (us a step one at a time / two: 256 cells of 321 hh CVs
@@ -493,8 +496,8 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
                     h[u] = sh[q];
                     x[u] = sn[q];
                     bnl[u] = hh_hbm ? a.beta[pk.slot0 + d[u].slot] : s_nlb[u ? j2 : j];
-                    gna[u] = hh_hbm ? (d[u].hh >= 0 ? a.hh_gna[pk.hh0 + q] : 0.0) : s_gna[q];
-                    gk[u] = hh_hbm ? (d[u].hh >= 0 ? a.hh_gk[pk.hh0 + q] : 0.0) : s_gk[q];
+                    gna[u] = hh_hbm ? g_gna[q] : s_gna[q];
+                    gk[u] = hh_hbm ? g_gk[q] : s_gk[q];
                 }
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
