@@ -286,14 +286,15 @@ __device__ __forceinline__ void round_sync() {
         __syncthreads();
 }
 
-// The upward pass of the split solve over the thread's S slots.  Packs with
-// at most binary branch points run every slot in every round: in workgroups
-// of up to two waves one tree level a round (a branch adds its children's
-// contributions: two loads per slot and round), in larger workgroups, where
-// each round costs a barrier across more waves, two levels a round
-// (up2_load, up2_store: eight loads per slot and round, half the rounds).
-// Both store the same contributions bit for bit.  Other packs take one round
-// of the host's schedule at a time, each slot in its own round.
+// The upward pass of the split solve over the thread's S slots (in 512
+// threads at most two).  Packs with at most binary branch points run every slot
+// in every round: in workgroups of up to two waves one tree level a round (a
+// branch adds its children's contributions: two loads per slot and round), in
+// larger workgroups, where each round costs a barrier across more waves, two
+// levels a round (up2_load, up2_store: eight loads per slot and round, half the
+// rounds; in 512 threads only by the slots of those levels).  All store the
+// same contributions bit for bit.  Other packs take one round of the host's
+// schedule at a time, each slot in its own round.
 template <int T, int S, int L>
 __device__ __forceinline__ void up_pass(const PackDesc& pk, Slot<L>& g0, Slot<L>& g1, Slot<L>& g2, const double* sF,
                                         const double* sQ, double* sC, const int32_t* s_ch) {
@@ -324,22 +325,32 @@ __device__ __forceinline__ void up_pass(const PackDesc& pk, Slot<L>& g0, Slot<L>
         }
     } else if (pk.binary) {
         // after round r every level from nlev - 3 - 2 r down is final
-        for (int lv = pk.nlev - 3; lv >= -1; lv -= 2) {
+        if constexpr (T == 512) {
+            // only the two levels that become final take part (a wave's branches
+            // are mostly of one level, so the other waves skip the round): with
+            // every slot in every round the loads fill the LDS (22 levels, two
+            // slots: 660 cycles a round, 430 so; in 256 threads the tests cost
+            // more than they save)
+            for (int lv = pk.nlev - 3; lv >= -1; lv -= 2) {
+                Up2In u0, u1;
+                const bool b0 = g0.lev == lv || g0.lev == lv + 1;
+                const bool b1 = S > 1 && (g1.lev == lv || g1.lev == lv + 1);
+                if (b0) u0 = up2_load<L>(g0, sF, sQ, sC);
+                if (b1) u1 = up2_load<L>(g1, sF, sQ, sC);
+                if (b0) up2_store<L>(g0, u0, sC);
+                if (b1) up2_store<L>(g1, u1, sC);
+                round_sync<T>();
+            }
+            return;
+        }
+        for (int sr = 0; 2 * sr + 1 < pk.nlev; ++sr) {
             Up2In u0, u1, u2;
-            // in 512 threads only the two levels that become final take part
-            // (a wave's branches are mostly of one level, so the other waves
-            // skip the round): with every slot in every round the loads fill
-            // the LDS (22 levels, two slots: 660 cycles a round, 430 so;
-            // with 256 threads the tests cost more than they save)
-            const bool b0 = T < 512 || g0.lev == lv || g0.lev == lv + 1;
-            const bool b1 = S > 1 && (T < 512 || g1.lev == lv || g1.lev == lv + 1);
-            const bool b2 = S > 2 && (T < 512 || g2.lev == lv || g2.lev == lv + 1);
-            if (b0) u0 = up2_load<L>(g0, sF, sQ, sC);
-            if (b1) u1 = up2_load<L>(g1, sF, sQ, sC);
-            if (b2) u2 = up2_load<L>(g2, sF, sQ, sC);
-            if (b0) up2_store<L>(g0, u0, sC);
-            if (b1) up2_store<L>(g1, u1, sC);
-            if (b2) up2_store<L>(g2, u2, sC);
+            u0 = up2_load<L>(g0, sF, sQ, sC);
+            if constexpr (S > 1) u1 = up2_load<L>(g1, sF, sQ, sC);
+            if constexpr (S > 2) u2 = up2_load<L>(g2, sF, sQ, sC);
+            up2_store<L>(g0, u0, sC);
+            if constexpr (S > 1) up2_store<L>(g1, u1, sC);
+            if constexpr (S > 2) up2_store<L>(g2, u2, sC);
             round_sync<T>();
         }
     } else {
@@ -367,7 +378,8 @@ __device__ __forceinline__ void grounded_store(const Slot<L>& g, double* sY, dou
 }
 
 // The downward pass: two tree levels a round, shallowest first, every slot
-// in every round (down_load, down_store).  With the root final beforehand
+// in every round (down_load, down_store), with two slots of 512 threads only
+// those of the round's levels.  With the root final beforehand
 // (grounded_store), after round r every level up to 2 r + 2 is final.
 template <int T, int S, int L>
 __device__ __forceinline__ void down_pass(const PackDesc& pk, Slot<L>& g0, Slot<L>& g1, Slot<L>& g2, const double* sY,
@@ -375,12 +387,7 @@ __device__ __forceinline__ void down_pass(const PackDesc& pk, Slot<L>& g0, Slot<
     if constexpr (T == 512 && S > 1) {  // only the two levels of the round, as going up
         for (int lv = 1; lv < pk.nlev; lv += 2) {
             if (g0.lev == lv || g0.lev == lv + 1) down_store<L>(g0, down_load<L>(g0, sY, sX), sX);
-            if constexpr (S > 1) {
-                if (g1.lev == lv || g1.lev == lv + 1) down_store<L>(g1, down_load<L>(g1, sY, sX), sX);
-            }
-            if constexpr (S > 2) {
-                if (g2.lev == lv || g2.lev == lv + 1) down_store<L>(g2, down_load<L>(g2, sY, sX), sX);
-            }
+            if (g1.lev == lv || g1.lev == lv + 1) down_store<L>(g1, down_load<L>(g1, sY, sX), sX);
             round_sync<T>();
         }
         return;
