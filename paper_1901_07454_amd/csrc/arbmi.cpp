@@ -433,7 +433,8 @@ int Sim::advance(int64_t n, const RecordArgs* rec) {
 
 StateShape Sim::state_shape() const {
     StateShape sh;
-    if (cfg.coef_mode == 3 && !timed && p.block_threads == 0 && p.cells_per_pack == 0 && cfg.block_threads != 256)
+    if (cfg.coef_mode == 3 && !timed && p.block_threads == 0 && p.cells_per_pack == 0 &&
+        (cfg.block_threads != 256 || L.repacked))
         sh.magic = kStateMagic ^ (uint64_t(cfg.block_threads / 64) << 56);
     if (long_cut) sh.magic = kStateMagic ^ (uint64_t(cfg.block_threads / 64 + 128) << 56);  // streamed before
     sh.K = K;
@@ -636,6 +637,7 @@ static int lower_planned(const ModelView& m, const arb_params& p, const Plan& pl
                            m.n_ic, p, opt, L, err);
     };
     opt.grads = opt.grads || plan.long_cut;
+    opt.wide_slots = plan.long_cut ? 0 : plan.wide_slots;
     int rc = lower();
     if (rc == ARB_OK && L.coef_mode == 3 &&
         !has_reg_step(L.block_threads, L.reg_slots, L.reg_len, opt.grads && !plan.long_cut, !L.gen_mech.empty())) {
@@ -648,6 +650,7 @@ static int lower_planned(const ModelView& m, const arb_params& p, const Plan& pl
         (err.find("LDS") != std::string::npos || err.find("register") != std::string::npos)) {
         opt.coef_mode = 2;
         opt.reg_slots = 0;
+        opt.wide_slots = 0;
         opt.block_threads = p.block_threads ? p.block_threads : 256;
         opt.max_cells_per_pack = std::max<int64_t>(1, plan.fallback_cells_per_pack);
         opt.lds_budget = plan.fallback_lds_budget;

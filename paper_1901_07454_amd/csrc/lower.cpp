@@ -360,7 +360,7 @@ int lower_model(const arb_cell* cells, int32_t n_cells, const arb_branch* br, in
     // is longer than the registers hold.
     struct Item { int32_t c, b; int len; };
     struct RoundPlan { std::vector<Item> items; int t0 = 0, j = 0, len = 0; };
-    const int S = opt.reg_slots;
+    int S = opt.reg_slots;
     auto build_rounds = [&](const std::vector<int32_t>& cs, std::vector<RoundPlan>& out) -> bool {
         out.clear();
         int maxd = 0;
@@ -512,6 +512,12 @@ int lower_model(const arb_cell* cells, int32_t n_cells, const arb_branch* br, in
             // a cell alone always makes a pack
             bool fits = cur.cells.empty() || (int64_t(trial.cells.size()) <= max_cells && trial.nin <= kPackInMax);
             if (fits && !cur.cells.empty()) fits = exact_lds(trial, coef_mode) <= opt.lds_budget;
+            if (!fits && opt.wide_slots > 0 && !L.repacked && int64_t(trial.cells.size()) <= T &&
+                trial.nin <= kPackInMax) {
+                S = opt.wide_slots;
+                L.repacked = exact_lds(trial, coef_mode) <= opt.lds_budget;
+                S = opt.reg_slots;
+            }
             if (!fits) {
                 if (!cur.cells.empty()) plans.push_back(cur);
                 cur = PackPlan();

@@ -102,6 +102,7 @@ struct Lowered {
     int32_t min_delay = 0, max_delay = 0;
     int64_t max_in_per_pack = 0;              // incoming connections of the busiest pack
     int64_t n_hh_total = 0;
+    bool repacked = false;                    // max_cells_per_pack or the slots kept a cell out of a pack (wide_slots)
     int64_t n_sum = 0;                        // conductance sums of every pack (PackDesc::sum0)
 };
 
@@ -113,6 +114,8 @@ struct LowerOptions {
     int64_t max_cells_per_pack = int64_t(1) << 30;
     int32_t reg_slots = 0;            // register-resident layout: branches per thread (0 = LDS layout)
     int32_t reg_len = 8;              // and the longest branch it takes
+    int32_t wide_slots = 0;           // if > 0: whether any number of cells, with this many slots, would
+                                      // be packed otherwise is noted (Lowered::repacked)
     bool grads = false;               // packs must also fit the adjoint kernel (register layout:
                                       // its LDS, and synapse state in LDS)
     // variable time step: continuous connection delays (ms, input order) and
@@ -137,9 +140,10 @@ std::string verify_layout(const Lowered& lw);
 // time), spike history (counts, gids, steps), generated mechanisms' states.
 constexpr uint64_t kStateMagic = 0x41524233535441ull;
 struct StateShape {
-    // kStateMagic, or a value of its own where the library chose a workgroup
-    // of other than 256 threads by itself: blobs written when the default was
-    // 256 threads hold the same CVs in another order
+    // kStateMagic, or a value of its own where the library by itself chose a
+    // workgroup of other than 256 threads, or filled it less than it can be:
+    // blobs written when the default was 256 threads, filled, hold the same
+    // CVs in another order
     uint64_t magic = kStateMagic;
     int32_t K = 1;            // epoch steps
     int32_t bk_cap = 0;       // network events per pack and epoch

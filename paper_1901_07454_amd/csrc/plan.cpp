@@ -142,6 +142,7 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
             // one wave cost what one costs (16,000 of them 4.1 against 11.2
             // us a step).  Cells that differ much in size (T = 256) fill a
             // workgroup up to half the LDS, unless every cell can have a CU.
+            if (T == 256) pl.wide_slots = pl.reg_len == 8 ? (tasks <= 2 * T ? 2 : 3) : 1;
             if (pair) {
                 pl.max_cells_per_pack = pair;
             } else if (T >= 256 && tasks > slots * 128) {

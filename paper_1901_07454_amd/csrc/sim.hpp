@@ -27,6 +27,7 @@ struct Plan {
     int64_t lds_hard_max = 160 * 1024;
     int64_t max_cells_per_pack = 64;
     int reg_slots = 0, reg_len = 8;
+    int wide_slots = 0;     // 256 threads by the library's choice: the slots of an explicit 256 (LowerOptions)
     bool long_cut = false;  // branches longer than the registers, cut by the library's choice
     int64_t fallback_cells_per_pack = 1;  // streamed mode, if the chosen layout fails
     int64_t fallback_lds_budget = 0;
