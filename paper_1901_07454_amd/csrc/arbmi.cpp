@@ -662,7 +662,8 @@ static int lower_planned(const ModelView& m, const arb_params& p, const Plan& pl
     return rc;
 }
 
-int build_sim(const ModelView& m, const arb_params& pp, const DeviceLimits& d, Sim** out, std::string& err) {
+int build_sim(const ModelView& m, const arb_params& pp, const DeviceLimits& d, Sim** out, std::string& err,
+              const Plan* as) {
     const arb_params* p = &pp;
     *out = nullptr;
     Sim* s = new Sim();
@@ -671,7 +672,8 @@ int build_sim(const ModelView& m, const arb_params& pp, const DeviceLimits& d, S
     s->device = d.dev;
     s->n_cu = d.n_cu;
     s->lds_max = d.lds_max;
-    const Plan plan = choose_plan(m.cells, m.n_cells, m.br, m.n_br, m.syn, m.n_syn, *p, d.lds_max, d.n_cu);
+    const Plan plan =
+        as ? *as : choose_plan(m.cells, m.n_cells, m.br, m.n_br, m.syn, m.n_syn, *p, d.lds_max, d.n_cu);
     LowerOptions opt;
     opt.block_threads = plan.block_threads;
     opt.coef_mode = plan.coef_mode;

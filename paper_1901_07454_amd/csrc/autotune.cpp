@@ -1,6 +1,7 @@
 // autotune.cpp -- choose the step kernel's launch shape by measurement.
 //
 // Candidates are (coefficient mode, threads per workgroup, cells per pack):
+// the library's own shape for the model (0, 0, 0; which may be 512 threads),
 // register-resident coefficients for every workgroup size where the branches
 // fit the registers, streamed coefficients at two pack sizes, and
 // LDS-resident coefficients.  Each candidate is built for a strided sample of
@@ -56,7 +57,7 @@ uint64_t shape_key(const ModelView& m, const DeviceLimits& d, const arb_params& 
     mix(uint64_t(d.n_cu));
     mix(uint64_t(d.lds_max));
     mix(uint64_t((p.flags & ARB_FLAG_GRADIENTS) ? 1 : 0));
-    mix(7);  // version of the candidate set and kernels
+    mix(8);  // version of the candidate set and kernels
     return h;
 }
 
@@ -157,17 +158,21 @@ Sample make_sample(const ModelView& m, int32_t n_sample) {
 }
 
 // CV-updates per second of one candidate on the sample, or 0 if it fails
-double time_candidate(const Sample& smp, const arb_params& base, const DeviceLimits& d, const Candidate& c) {
+double time_candidate(const ModelView& m, const Sample& smp, const arb_params& base, const DeviceLimits& d,
+                      const Candidate& c) {
     arb_params p = base;
-    p.flags &= ~(ARB_FLAG_AUTOTUNE | ARB_FLAG_TIME_KERNELS | ARB_FLAG_GRAPH);
+    p.flags &= ~(ARB_FLAG_TIME_KERNELS | ARB_FLAG_GRAPH);
     p.coef_mode = c.coef_mode;
     p.block_threads = c.threads;
     p.cells_per_pack = c.cells_per_pack;
     p.epoch_steps = 0;
+    const Plan plan = trial_plan(m, smp.view(), p, d);
+    p.flags &= ~ARB_FLAG_AUTOTUNE;  // a mode that does not fit is refused, not replaced
     Sim* s = nullptr;
     std::string err;
-    if (build_sim(smp.view(), p, d, &s, err) != ARB_OK || !s) return 0.0;
-    if (s->cfg.coef_mode != c.coef_mode) {  // fell back to another mode
+    if (build_sim(smp.view(), p, d, &s, err, &plan) != ARB_OK || !s) return 0.0;
+    // fell back to another mode (the streamed shapes are candidates themselves)
+    if (s->cfg.coef_mode != (c.coef_mode ? c.coef_mode : 3)) {
         destroy_sim(s);
         return 0.0;
     }
@@ -194,7 +199,7 @@ double time_candidate(const Sample& smp, const arb_params& base, const DeviceLim
 arb_params autotune(const ModelView& m, const arb_params& p, const DeviceLimits& d) {
     arb_params out = p;
     const uint64_t key = shape_key(m, d, p);
-    Candidate best{0, 0, 0};
+    Candidate best{0, 0, 0};  // as planned
     if (!cache_lookup(key, best)) {
         // enough cells for several waves of workgroups on every CU, so that
         // the last, partial wave weighs about as much as in the full model;
@@ -215,13 +220,13 @@ arb_params autotune(const ModelView& m, const arb_params& p, const DeviceLimits&
         }
         const int fill256 = int(std::max<int64_t>(1, 256 / max_width));
         const std::vector<Candidate> cands = {
-            {3, 0, 0},  // the library's own shape, which may be 512 threads
+            {0, 0, 0},
             {3, 256, 0}, {3, 128, 0}, {3, 64, 0}, {3, 64, 1}, {3, 128, 1},
             {2, 256, fill256}, {2, 256, std::max(1, fill256 / 2)}, {2, 128, std::max(1, fill256 / 2)},
             {2, 64, 1}, {1, 64, 1}, {1, 256, 0}};
         double best_rate = 0.0;
         for (const Candidate& c : cands) {
-            const double r = time_candidate(smp, p, d, c);
+            const double r = time_candidate(m, smp, p, d, c);
             if (r > best_rate) {
                 best_rate = r;
                 best = c;

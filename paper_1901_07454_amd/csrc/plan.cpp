@@ -189,4 +189,10 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
     return pl;
 }
 
+Plan trial_plan(const ModelView& full, const ModelView& sample, const arb_params& p, const DeviceLimits& d) {
+    const bool own = p.coef_mode == 0 && p.block_threads == 0 && p.cells_per_pack == 0;
+    const ModelView& m = own ? full : sample;
+    return choose_plan(m.cells, m.n_cells, m.br, m.n_br, m.syn, m.n_syn, p, d.lds_max, d.n_cu);
+}
+
 }  // namespace arbmi

@@ -187,8 +187,15 @@ struct DeviceLimits {
     int n_cu = 256;
 };
 
-// Lower and upload a model with the launch parameters in p (0 = planned).
-int build_sim(const ModelView& m, const arb_params& p, const DeviceLimits& d, Sim** out, std::string& err);
+// The plan under which the autotuner times launch parameters p on a sample of
+// a model: with everything left to the library the full model's, whose rules
+// count its cells, for that is the shape the model will run in.
+Plan trial_plan(const ModelView& full, const ModelView& sample, const arb_params& p, const DeviceLimits& d);
+
+// Lower and upload a model with the launch parameters in p (0 = planned, or as
+// in `plan`).
+int build_sim(const ModelView& m, const arb_params& p, const DeviceLimits& d, Sim** out, std::string& err,
+              const Plan* plan = nullptr);
 void destroy_sim(Sim* s);
 // Time candidate launch shapes on a sample of the model's cells; returns p
 // with block_threads, coef_mode and cells_per_pack set to the fastest.
