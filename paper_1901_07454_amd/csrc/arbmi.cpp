@@ -683,6 +683,7 @@ int build_sim(const ModelView& m, const arb_params& pp, const DeviceLimits& d, S
     opt.reg_slots = plan.coef_mode == 3 ? plan.reg_slots : 0;
     opt.reg_len = plan.reg_len;
     opt.grads = (p->flags & ARB_FLAG_GRADIENTS) != 0;
+    opt.n_cu = d.n_cu;
     opt.conn_delay_ms = m.conn_delay_ms;
     opt.ev_t_ms = m.ev_t_ms;
     const bool timed = m.conn_delay_ms != nullptr || m.ev_t_ms != nullptr;
@@ -1042,6 +1043,7 @@ int arb_plan_layout(const arb_cell* cells, int32_t n_cells, const arb_branch* br
     opt.reg_slots = plan.coef_mode == 3 ? plan.reg_slots : 0;
     opt.reg_len = plan.reg_len;
     opt.grads = (p->flags & ARB_FLAG_GRADIENTS) != 0;
+    opt.n_cu = d.n_cu;
     Lowered L;
     std::string err;
     bool long_cut = false;

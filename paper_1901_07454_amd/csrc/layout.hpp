@@ -119,8 +119,7 @@ inline int64_t pack_lds_bytes(const PackDesc& D, int coef_mode) {
                             (D.hh_global ? 3 : 5) * int64_t(D.nhh) +
                             (D.hh_global ? 0 : int64_t(D.nnl)) + (D.binary ? 3 : 2) * (int64_t(D.ntk) + 2) +
                             (D.syn_sum ? int64_t(D.nnl) : 0) + D.ngen;
-        return 8 * dbl + 16 * int64_t(D.nnl) + (D.binary ? 0 : 4 * int64_t(D.nch)) + 4 * int64_t(D.nhh) +
-               (D.ngen ? 4 * (int64_t(D.nnl) + 1) : 0);
+        return 8 * dbl + 16 * int64_t(D.nnl) + (D.binary ? 0 : 4 * int64_t(D.nch)) + 4 * int64_t(D.nhh);
     }
     const bool cl = coef_mode == 1;
     const int64_t dbl = (cl ? 6 : 2) * int64_t(D.nslot) + int64_t(D.nsyn) + 3 * int64_t(D.nhh) +

@@ -908,8 +908,25 @@ int lower_model(const arb_cell* cells, int32_t n_cells, const arb_branch* br, in
                 while (L.gen_rec.size() % kGenChunk)
                     L.gen_rec.push_back({L.gen_row[last], L.gen_slot[last], -1, half, 0.0, 0.0});
             }
+            // The instances' currents in LDS, unless it has no room, or (two
+            // waves and more) they leave fewer workgroups on a CU than its
+            // registers take (two waves per SIMD with one slot of 8 CVs, one
+            // otherwise) and the launch a third more rounds of them (8192 cells
+            // of 249 CVs filling 256 threads to half the LDS: 58.6 us a step
+            // with the currents in LDS, one workgroup on a CU, 46.9 in HBM).
+            // At equal occupancy LDS is faster: 4096 cells of 1017 CVs, 256
+            // threads, 78 us and 94.
+            int slots = 1;
+            for (int32_t r = 0; r < D.nrd; ++r) slots = std::max(slots, L.rounds[D.rd0 + r].j + 1);
+            const int64_t by_reg = std::max<int64_t>(1, (slots * opt.reg_len <= 8 ? 8 : 4) * 64 / T);
+            auto rounds = [&](int64_t bytes) {
+                const int64_t at_once = opt.n_cu * std::min(by_reg, std::max<int64_t>(1, opt.lds_hard_max / bytes));
+                return (n_packs + at_once - 1) / at_once;
+            };
+            const int64_t without = pack_lds_bytes(D, L.coef_mode);
             D.ngen = q1 - q0;
-            if (pack_lds_bytes(D, L.coef_mode) > opt.lds_hard_max) D.ngen = 0;
+            const int64_t with = pack_lds_bytes(D, L.coef_mode);
+            if (with > opt.lds_hard_max || (T > 64 && 3 * rounds(with) >= 4 * rounds(without))) D.ngen = 0;
         }
         L.gen_rec_pk.push_back(int32_t(L.gen_rec.size()));
         const size_t ni = L.gen_mech.size();

@@ -114,6 +114,7 @@ struct LowerOptions {
     int64_t max_cells_per_pack = int64_t(1) << 30;
     int32_t reg_slots = 0;            // register-resident layout: branches per thread (0 = LDS layout)
     int32_t reg_len = 8;              // and the longest branch it takes
+    int32_t n_cu = 256;               // compute units (where generated instances' currents are kept)
     int32_t wide_slots = 0;           // if > 0: whether any number of cells, with this many slots, would
                                       // be packed otherwise is noted (Lowered::repacked)
     bool grads = false;               // packs must also fit the adjoint kernel (register layout:

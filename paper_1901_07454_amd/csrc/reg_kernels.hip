@@ -114,7 +114,6 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
     NlDesc* s_nl = reinterpret_cast<NlDesc*>(s_cur + (M ? pk.ngen : 0));
     int32_t* s_ch = reinterpret_cast<int32_t*>(s_nl + pk.nnl);  // children's tasks (other packs)
     int32_t* s_hhs = s_ch + (pk.binary ? 0 : pk.nch);          // per hh instance: its CV's slot
-    int32_t* s_goff = s_hhs + pk.nhh;                          // each entry's first instance (ngen)
 
     // One conductance sum per nonlinear CV (kSumMinDecay in layout.hpp),
     // instead of streaming every conductance each step, which
@@ -170,11 +169,14 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
         }
     }
     for (int i = tid; i < pk.nnl; i += T) {
-        const NlDesc d = a.nl[pk.nl0 + i];
-        s_nl[i] = d;
+        NlDesc d = a.nl[pk.nl0 + i];
         if (!hh_hbm) s_nlb[i] = a.beta[pk.slot0 + d.slot];
         if (d.hh >= 0) s_hhs[d.hh] = vix(d.slot);
         if (sums) s_sum[i] = a.syn_sum[pk.sum0 + i];
+        // with currents in LDS an entry's first instance rides in its slot's
+        // high bits (LDS holds fewer than 2^16 of either)
+        if (M && pk.ngen) d.slot |= (a.gen_off[pk.nl0 + i] - a.gen_pk[p]) << 16;
+        s_nl[i] = d;
     }
     if (!pk.binary)
         for (int i = tid; i < pk.nch; i += T) s_ch[i] = a.ch_task[pk.ch0 + i];
@@ -295,10 +297,6 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
                 a.gen_cur[gq0 + q] = g.r[h].w * cur[h];
         }
     };
-    if constexpr (M) {
-        if (pk.ngen)
-            for (int i = tid; i <= pk.nnl; i += T) s_goff[i] = a.gen_off[pk.nl0 + i] - gq0;
-    }
     __syncthreads();
     if constexpr (M) {
         for (int e = ge; e < ge1; e += 2 * T) {
@@ -512,7 +510,9 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
             }
         } else {
             for (int j = tid; j < pk.nnl; j += T) {
-                const NlDesc d = s_nl[j];
+                NlDesc d = s_nl[j];
+                const int q0 = M ? int(uint32_t(d.slot) >> 16) : 0;
+                if constexpr (M) d.slot &= 0xffff;
                 const double v = sV[vix(d.slot)];
                 double I = 0.0, bnl;
                 if (hh_hbm) {
@@ -533,9 +533,10 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
                     }
                 }
                 if constexpr (M) {
-                    if (pk.ngen)
-                        for (int q = s_goff[j]; q < s_goff[j + 1]; ++q) I += s_cur[q];
-                    else
+                    if (pk.ngen) {
+                        const int q1 = j + 1 < pk.nnl ? int(uint32_t(s_nl[j + 1].slot) >> 16) : pk.ngen;
+                        for (int q = q0; q < q1; ++q) I += s_cur[q];
+                    } else
                         for (int q = a.gen_off[pk.nl0 + j]; q < a.gen_off[pk.nl0 + j + 1]; ++q) I += a.gen_cur[q];
                 }
                 synapses(j, d, v, I);
