@@ -173,9 +173,14 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
         if (!hh_hbm) s_nlb[i] = a.beta[pk.slot0 + d.slot];
         if (d.hh >= 0) s_hhs[d.hh] = vix(d.slot);
         if (sums) s_sum[i] = a.syn_sum[pk.sum0 + i];
-        // with currents in LDS an entry's first instance rides in its slot's
-        // high bits (LDS holds fewer than 2^16 of either)
-        if (M && pk.ngen) d.slot |= (a.gen_off[pk.nl0 + i] - a.gen_pk[p]) << 16;
+        // with currents in LDS an entry's first instance and their number ride
+        // in the high halves of its slot and hh instance (LDS holds fewer than
+        // 2^15 of any of them)
+        if (M && pk.ngen) {
+            const int q0 = a.gen_off[pk.nl0 + i];
+            d.slot |= (q0 - a.gen_pk[p]) << 16;
+            d.hh = (d.hh & 0xffff) | (a.gen_off[pk.nl0 + i + 1] - q0) << 16;
+        }
         s_nl[i] = d;
     }
     if (!pk.binary)
@@ -512,7 +517,11 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
             for (int j = tid; j < pk.nnl; j += T) {
                 NlDesc d = s_nl[j];
                 const int q0 = M ? int(uint32_t(d.slot) >> 16) : 0;
-                if constexpr (M) d.slot &= 0xffff;
+                const int q1 = M ? q0 + int(uint32_t(d.hh) >> 16) : 0;
+                if constexpr (M) {
+                    d.slot &= 0xffff;
+                    d.hh = int16_t(d.hh);
+                }
                 const double v = sV[vix(d.slot)];
                 double I = 0.0, bnl;
                 if (hh_hbm) {
@@ -534,7 +543,6 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
                 }
                 if constexpr (M) {
                     if (pk.ngen) {
-                        const int q1 = j + 1 < pk.nnl ? int(uint32_t(s_nl[j + 1].slot) >> 16) : pk.ngen;
                         for (int q = q0; q < q1; ++q) I += s_cur[q];
                     } else
                         for (int q = a.gen_off[pk.nl0 + j]; q < a.gen_off[pk.nl0 + j + 1]; ++q) I += a.gen_cur[q];
