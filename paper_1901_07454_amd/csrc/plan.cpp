@@ -13,7 +13,7 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
     // largest cell (CVs), widest branch level, longest branch, most branches,
     // branches of all cells, most CVs with nonlinear or point currents
     int64_t max_cv = 1, max_width = 1, max_len = 1, max_tasks = 1, max_tasks8 = 1, all_tasks8 = 0, max_nl = 0,
-            max_hh = 0, max_lds = 1;
+            max_hh = 0, max_syn = 0, max_lds = 1;
     std::vector<int> depth, count;
     std::vector<int64_t> n_syn_of(size_t(std::max(n_cells, 0)), 0);
     for (int64_t q = 0; q < n_syn && syn; ++q)
@@ -39,6 +39,7 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
         max_tasks8 = std::max(max_tasks8, seg8);
         all_tasks8 += seg8;
         max_hh = std::max(max_hh, hh);
+        max_syn = std::max(max_syn, n_syn_of[c]);
         const int64_t nl = p.n_densities > 0 ? n : std::min(n, hh + n_syn_of[c]);
         max_nl = std::max(max_nl, nl);
         // the register layout's LDS of the cell, near enough (pack_lds_bytes)
@@ -112,6 +113,20 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
                 T = 256;
                 pair = int64_t(n_cells) * (T / 64) <= 8 * int64_t(n_cu) ? 1 : 2;
             }
+            const int64_t avg = std::max<int64_t>(1, all_tasks8 / std::max(1, n_cells));
+            // Cells with generated mechanisms, two or more for each CU: 256
+            // threads shared by cells of up to four nonlinear CVs a thread,
+            // which keep its waves evenly busy with instances and its lanes with
+            // branches (us a step, a wave for each cell / so / 256 threads
+            // filled to half the LDS: 8192 cells of 57 CVs 28.6 / 11.8 / 18.4, of
+            // 121 37.8 / 21.6 / 29.5, of 249 50.3 / 39.5 / 47.1; 600 cells of 121
+            // 7.7 / 5.7 / 16.2), and whose synapses stay in LDS together, as
+            // generated mechanisms need.
+            int64_t share = 0;
+            if (p.n_densities > 0 && pl.reg_len == 8)
+                share = std::min({256 / avg, 4 * 256 / std::max<int64_t>(1, max_nl), int64_t(n_cells) / n_cu,
+                                  kSynLdsMax / (24 * std::max<int64_t>(1, max_syn))});
+            if (T < 256 && share >= 2) T = 256;
             const int want = (max_nl > 128 || tasks > 128) ? 256 : max_nl > 64 ? 128 : 64;
             while (T < want && int64_t(n_cells) * (2 * T / 64) <= 4 * int64_t(n_cu)) T *= 2;
             // Cells of more than 256 branches in 512 threads, two waves per SIMD,
@@ -145,10 +160,11 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
             if (T == 256) pl.wide_slots = pl.reg_len == 8 ? (tasks <= 2 * T ? 2 : 3) : 1;
             if (pair) {
                 pl.max_cells_per_pack = pair;
+            } else if (T == 256 && share >= 2) {
+                pl.max_cells_per_pack = share;
             } else if (T >= 256 && tasks > slots * 128) {
                 pl.max_cells_per_pack = n_cells <= n_cu ? 1 : T;
             } else {
-                const int64_t avg = std::max<int64_t>(1, all_tasks8 / std::max(1, n_cells));
                 int64_t c = std::min(pl.reg_slots * T / avg, T / std::max<int64_t>(1, max_nl));
                 // while that leaves SIMDs idle, no more cells than have a
                 // thread for every gate
