@@ -435,7 +435,7 @@ StateShape Sim::state_shape() const {
     StateShape sh;
     if (cfg.coef_mode == 3 && !timed && p.block_threads == 0 && p.cells_per_pack == 0 &&
         (cfg.block_threads != 256 || L.repacked))
-        sh.magic = kStateMagic ^ (uint64_t(cfg.block_threads / 64) << 56);
+        sh.magic = kStateMagic ^ (uint64_t(cfg.block_threads / 64 + (estimated ? 32 : 0)) << 56);
     if (long_cut) sh.magic = kStateMagic ^ (uint64_t(cfg.block_threads / 64 + 128) << 56);  // streamed before
     sh.K = K;
     sh.bk_cap = bk_cap;
@@ -714,6 +714,7 @@ int build_sim(const ModelView& m, const arb_params& pp, const DeviceLimits& d, S
         }
     } else {
         rc = lower_planned(m, *p, plan, opt, s->L, s->long_cut, err);
+        s->estimated = plan.estimated;
     }
     if (rc != ARB_OK) {
         delete s;

@@ -142,7 +142,8 @@ std::string verify_layout(const Lowered& lw);
 constexpr uint64_t kStateMagic = 0x41524233535441ull;
 struct StateShape {
     // kStateMagic, or a value of its own where the library by itself chose a
-    // workgroup of other than 256 threads, or filled it less than it can be:
+    // workgroup of other than 256 threads, or filled it less than it can be (by
+    // rule, or by the estimated step: Sim::state_shape):
     // blobs written when the default was 256 threads, filled, hold the same
     // CVs in another order
     uint64_t magic = kStateMagic;

@@ -1,10 +1,60 @@
 // plan.cpp -- launch shape and packing limits for a model.
 #include <algorithm>
+#include <cmath>
 #include <vector>
 
 #include "sim.hpp"
 
 namespace arbmi {
+
+namespace {
+
+// A model's mean cell, for the estimate below.
+struct MeanCell {
+    double tasks, hh, nl, syn;  // branches with the soma, CVs with hh, nonlinear CVs, synapses
+    int levels;                 // of the deepest tree, the soma's with them
+};
+
+// LDS of a workgroup of c such cells with at most binary branch points.
+int64_t mean_lds(int len, int64_t c, const MeanCell& m) {
+    PackDesc D{};
+    D.ntk = int32_t(double(c) * m.tasks);
+    D.nslot = len * D.ntk;
+    D.nhh = int32_t(double(c) * m.hh);
+    D.nnl = int32_t(double(c) * m.nl);
+    D.nsyn = int32_t(double(c) * m.syn);
+    D.binary = 1;
+    return pack_lds_bytes(D, 3);
+}
+
+// Time of a step (us) of n cells, c to a workgroup of T threads whose branches
+// take `len` registers: the workgroups a CU holds at once by registers and LDS
+// run in rounds of that many, and a round takes the time of its chain of phases
+// (local solve, tree levels, nonlinear CVs and gates one after another in a
+// thread) and of its instructions on the SIMDs, which overlap in part.  The
+// constants are a fit to 14,400 measured shapes of 917 models (30 to 9,000 cells
+// of 1 to 126 branches of 4, 8, 13 or 16 CVs, none to all of them hh, 1 to 120
+// synapses): 12% off in the mean, 6% at the median.
+double step_us(int T, int len, int64_t c, int64_t n, int n_cu, int64_t lds_max, const MeanCell& m) {
+    const double tasks = double(c) * m.tasks, hh = double(c) * m.hh, nl = double(c) * m.nl;
+    const double held = std::ceil(tasks / T) * len / 8;  // 8-CV branches a thread holds
+    const int64_t lds = mean_lds(len, c, m);
+    const int by_reg = (held <= 1 ? 3 : held <= 2 ? 2 : 1) * 256 / T;
+    const int64_t on_cu = std::max<int64_t>(1, std::min<int64_t>(by_reg, lds_max / lds));
+    const bool spread = hh <= kSpreadHH;  // a thread for every gate
+    const double chain = (T == 64 ? 0.91 : T == 128 ? 1.1 : 1.07) + 0.12 * (m.levels + 1) + 0.23 * (held - 1) +
+                         (spread ? 0.17 : 0.92 * std::ceil(hh / T)) + 0.28 * std::ceil(nl / T);
+    const double waves = T / 64.0;
+    const double issue = 0.24 * held + (spread ? 0.085 : 0.31 * std::ceil(hh / 64) / waves) +
+                         0.15 * std::ceil(nl / 64) / waves;
+    auto round = [&](int64_t on) {
+        return std::pow(std::pow(chain, 1.2) + std::pow(double(on) * waves / 4 * issue, 1.2), 1 / 1.2);
+    };
+    const int64_t packs = (n + c - 1) / c, at_once = n_cu * on_cu, rest = packs % at_once;
+    return double(packs / at_once) * round(on_cu) + (rest ? round((rest + n_cu - 1) / n_cu) : 0.0);
+}
+
+}  // namespace
 
 Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, int64_t n_br, const arb_synapse* syn,
                  int64_t n_syn, const arb_params& p, int64_t lds_max, int n_cu) {
@@ -13,7 +63,8 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
     // largest cell (CVs), widest branch level, longest branch, most branches,
     // branches of all cells, most CVs with nonlinear or point currents
     int64_t max_cv = 1, max_width = 1, max_len = 1, max_tasks = 1, max_tasks8 = 1, all_tasks8 = 0, max_nl = 0,
-            max_hh = 0, max_syn = 0, max_lds = 1;
+            max_hh = 0, max_syn = 0, max_lds = 1, max_depth = 0, all_tasks = 0, all_hh = 0, all_nl = 0,
+            all_syn = 0;
     std::vector<int> depth, count;
     std::vector<int64_t> n_syn_of(size_t(std::max(n_cells, 0)), 0);
     for (int64_t q = 0; q < n_syn && syn; ++q)
@@ -31,6 +82,7 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
             if (B.mech & ARB_MECH_HH) hh += std::max(0, B.n_cv);
             max_len = std::max<int64_t>(max_len, B.n_cv);
             depth[b] = (B.parent < 0 || B.parent >= b) ? 1 : depth[B.parent] + 1;
+            max_depth = std::max<int64_t>(max_depth, depth[b]);
             if (depth[b] <= C.n_branch) count[depth[b]]++;
         }
         for (int v : count) max_width = std::max<int64_t>(max_width, v);
@@ -40,8 +92,12 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
         all_tasks8 += seg8;
         max_hh = std::max(max_hh, hh);
         max_syn = std::max(max_syn, n_syn_of[c]);
+        all_tasks += C.n_branch + 1;
+        all_hh += hh;
+        all_syn += n_syn_of[c];
         const int64_t nl = p.n_densities > 0 ? n : std::min(n, hh + n_syn_of[c]);
         max_nl = std::max(max_nl, nl);
+        all_nl += nl;
         // the register layout's LDS of the cell, near enough (pack_lds_bytes)
         const int64_t syn_lds = 24 * n_syn_of[c] > kSynLdsMax ? 0 : 24 * n_syn_of[c];
         max_lds = std::max(max_lds, (128 + 24) * seg8 + syn_lds + 44 * hh + (p.n_densities > 0 ? 37 : 24) * nl);
@@ -171,6 +227,51 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
                 const int64_t spread = kSpreadHH / std::max<int64_t>(1, max_hh);
                 if (spread >= 1 && n_cells <= 4 * int64_t(n_cu) * spread) c = std::min(c, spread);
                 pl.max_cells_per_pack = std::max<int64_t>(1, c);
+            }
+            // The rules weigh one thing at a time, and lose to 256 threads
+            // filled to half the LDS where a last round of workgroups is nearly
+            // empty, or a wave that could take more cells has one.  For many
+            // similar cells that fit two waves, where the estimate says so, the
+            // shape with the least estimated step (us a step, filled / by the
+            // rules / so: 7578 cells of 40 CVs, 14 hh, 6.6 / 10.2 / 4.8; 5152 of
+            // 121, 65 hh, 8.1 / 13.0 / 7.9; 1443 of 1281, soma hh, 4.2 / 6.8 /
+            // 4.3).  Of 799 models of 256 cells and more, 84 were more than 3%
+            // slower by the rules than filled, and 21 are so.
+            const double n = std::max(1, n_cells);
+            const MeanCell mean{double(all_tasks) / n, double(all_hh) / n, double(all_nl) / n, double(all_syn) / n,
+                                int(max_depth) + 1};
+            const bool similar = double(max_tasks) <= 1.25 * mean.tasks + 1 && double(max_nl) <= 1.25 * mean.nl + 8;
+            if (n_cells >= n_cu && max_tasks <= 128 && max_len <= 16 && similar && !grads && p.n_densities == 0 &&
+                24 * max_syn <= kSynLdsMax) {
+                const int64_t cap = pl.reg_len == 8 ? 2 : 1;  // branches a thread holds
+                auto fits = [&](int threads, int64_t c) {
+                    return c == 1 || (c * max_tasks <= cap * threads && 24 * c * max_syn <= kSynLdsMax &&
+                                      c <= threads && mean_lds(pl.reg_len, c, mean) <= pl.lds_budget);
+                };
+                auto us = [&](int threads, int64_t c) {
+                    return step_us(threads, pl.reg_len, c, n_cells, n_cu, lds_max, mean);
+                };
+                int64_t fill = 1;  // cells of 256 threads filled
+                while (fits(256, fill + 1)) ++fill;
+                // (a shape has to win by more than the estimate's ties)
+                double least = 0.985 * us(pl.block_threads, std::min(pl.max_cells_per_pack, fill));
+                const bool lost = us(256, fill) < least;
+                int best_T = 0;
+                int64_t best_c = 0;
+                for (const int threads : {64, 128, 256})
+                    for (int64_t c = 1; c <= fill && lost; ++c) {
+                        if (max_tasks > cap * threads || !fits(threads, c) || us(threads, c) >= least) continue;
+                        least = us(threads, c);
+                        best_T = threads;
+                        best_c = c;
+                    }
+                if (best_T) {
+                    pl.estimated = true;
+                    pl.block_threads = best_T;
+                    pl.max_cells_per_pack = best_c;
+                    pl.reg_slots = pl.reg_len == 8 ? int((best_c * max_tasks + best_T - 1) / best_T) : 1;
+                    pl.wide_slots = best_T == 256 ? int(cap) : 0;
+                }
             }
             return pl;
         }

@@ -28,6 +28,7 @@ struct Plan {
     int64_t max_cells_per_pack = 64;
     int reg_slots = 0, reg_len = 8;
     int wide_slots = 0;     // 256 threads by the library's choice: the slots of an explicit 256 (LowerOptions)
+    bool estimated = false; // the shape of the least estimated step
     bool long_cut = false;  // branches longer than the registers, cut by the library's choice
     int64_t fallback_cells_per_pack = 1;  // streamed mode, if the chosen layout fails
     int64_t fallback_lds_budget = 0;
@@ -131,6 +132,7 @@ struct Sim : arb_sim_ {
     int capture_epoch_graph();
     // branches longer than the registers, cut into segments by the library's choice
     bool long_cut = false;
+    bool estimated = false;  // the launch shape was chosen by the estimated step (Plan)
     // variable time step (continuous event times; arb_build_cells_timed)
     bool timed = false;
     double *d_xe_t = nullptr, *d_bk_t = nullptr, *d_cr_delay_ms = nullptr;
