@@ -188,12 +188,15 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
             // Cells of more than 256 branches in 512 threads, two waves per SIMD,
             // where the kernels have it (uneven cells of up to 5000 CVs, us a
             // step with 256 threads / 512: 64 cells 14.2 / 11.2, 512 of them
-            // 15.2 / 12.1, 2000 of them 30.5 / 26.6): branches of up to 8 CVs, and
-            // where the caller asked for this layout no more of them than it
-            // takes with any other workgroup (an explicit request is honoured
-            // or refused).
+            // 15.2 / 12.1, 2000 of them 30.5 / 26.6), where each has a CU to
+            // itself by number or by LDS (256 threads let two share one: 312
+            // cells of 300 branches, 74 KB, 6.6 / 8.8, 403 of 450, 70 KB, 5.3 /
+            // 6.9; 404 of 378, 110 KB, 15.1 / 13.1).  Branches of up to 8 CVs,
+            // and where the caller asked for this layout no more of them than
+            // it takes with any other workgroup (an explicit request is
+            // honoured or refused).
             if (T == 256 && pl.reg_len == 8 && tasks > 256 && tasks <= (p.coef_mode == 3 ? 768 : 1024) &&
-                !grads && !pl.long_cut && p.n_densities == 0)
+                !grads && !pl.long_cut && p.n_densities == 0 && (n_cells <= n_cu || 2 * max_lds > lds_max))
                 T = 512;
             // Cells with generated mechanisms and more nonlinear CVs than 256
             // threads, where each has a CU to itself (by number, or by LDS):

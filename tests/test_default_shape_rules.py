@@ -1,0 +1,24 @@
+"""The default launch shape's rules that count workgroups on a CU: plans on the
+CPU, results against the oracle on the GPU."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1901_07454_amd import arbmi
+from tests.test_abi import _plan
+from tests.test_default_shape import _cells
+from workloads import gen
+
+
+def _shape(cells, **kw):
+    info = _plan(gen.assemble(cells, n_steps=10), **kw)
+    return info["block_threads"], info["reg_slots"], info["n_packs"]
+
+
+@pytest.mark.parametrize("n,branches,hh,shape", [
+    (256, 300, 0, (512, 1, 256)),   # a CU for each cell
+    (257, 300, 30, (256, 2, 257)),  # two of 62 KB share one
+    (300, 400, 17, (256, 2, 300)),  # 70 KB
+    (300, 380, 95, (512, 1, 300))])  # 110 KB: one to a CU either way
+def test_512_threads_where_a_cell_has_a_cu(n, branches, hh, shape):
+    assert _shape(_cells(1, branches, hh_branches=hh) * n) == shape
