@@ -103,6 +103,12 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
         max_lds = std::max(max_lds, (128 + 24) * seg8 + syn_lds + 44 * hh + (p.n_densities > 0 ? 37 : 24) * nl);
     }
     const bool grads = (p.flags & ARB_FLAG_GRADIENTS) != 0;
+    // some cell has too many synapses for LDS, and they are of more than one kind
+    // (near enough: the model's are)
+    bool streams = false;
+    if (24 * max_syn > kSynLdsMax)
+        for (int64_t q = 1; q < n_syn && !streams; ++q)
+            streams = syn[q].tau_ms != syn[0].tau_ms || syn[q].e_rev_mV != syn[0].e_rev_mV;
 
     // Streamed coefficients (mode 2): 16 B of LDS per CV, 256 threads, enough
     // cells per pack that the widest branch level fills the workgroup.  Also
@@ -183,6 +189,11 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
                 share = std::min({256 / avg, 4 * 256 / std::max<int64_t>(1, max_nl), int64_t(n_cells) / n_cu,
                                   kSynLdsMax / (24 * std::max<int64_t>(1, max_syn))});
             if (T < 256 && share >= 2) T = 256;
+            // Cells whose synapses stream from HBM each step want as many loads
+            // in flight as there are threads, and branches for all of them (914
+            // cells of 130 branches and 2177 synapses of two kinds: 30.5 us a
+            // step with 64 threads, 15.1 with 256).
+            if (T < 256 && streams && tasks > T) T = 256;
             const int want = (max_nl > 128 || tasks > 128) ? 256 : max_nl > 64 ? 128 : 64;
             while (T < want && int64_t(n_cells) * (2 * T / 64) <= 4 * int64_t(n_cu)) T *= 2;
             // Cells of more than 256 branches in 512 threads, two waves per SIMD,

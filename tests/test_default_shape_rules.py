@@ -22,3 +22,13 @@ def _shape(cells, **kw):
     (300, 380, 95, (512, 1, 300))])  # 110 KB: one to a CU either way
 def test_512_threads_where_a_cell_has_a_cu(n, branches, hh, shape):
     assert _shape(_cells(1, branches, hh_branches=hh) * n) == shape
+
+
+@pytest.mark.parametrize("branches,n_syn,same,shape", [
+    (130, 700, True, (64, 3, 600)),     # one conductance sum per CV
+    (130, 700, False, (256, 1, 600)),   # streamed: a thread for every branch
+    (63, 700, False, (64, 1, 600))])    # one wave has them
+def test_threads_for_streamed_synapses(branches, n_syn, same, shape):
+    d = _cells(1, branches)[0]
+    d.syn = [(-1, 0, 2.0, 0.0)] + [(q % branches, 0, 2.0 if same or q % 2 else 3.0, 0.0) for q in range(n_syn - 1)]
+    assert _shape([d] * 600) == shape
