@@ -194,6 +194,10 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
             // cells of 130 branches and 2177 synapses of two kinds: 30.5 us a
             // step with 64 threads, 15.1 with 256).
             if (T < 256 && streams && tasks > T) T = 256;
+            // Cells of which the largest, more than one wave takes, is more
+            // than twice the mean share 256 threads or more (below).
+            const bool mixed = tasks > slots * 64 && max_tasks > 2 * all_tasks / std::max(1, n_cells);
+            if (T < 256 && mixed) T = 256;
             const int want = (max_nl > 128 || tasks > 128) ? 256 : max_nl > 64 ? 128 : 64;
             while (T < want && int64_t(n_cells) * (2 * T / 64) <= 4 * int64_t(n_cu)) T *= 2;
             // Cells of more than 256 branches in 512 threads, two waves per SIMD,
@@ -207,7 +211,7 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
             // it takes with any other workgroup (an explicit request is
             // honoured or refused).
             if (T == 256 && pl.reg_len == 8 && tasks > 256 && tasks <= (p.coef_mode == 3 ? 768 : 1024) &&
-                !grads && !pl.long_cut && p.n_densities == 0 && (n_cells <= n_cu || 2 * max_lds > lds_max))
+                !grads && !pl.long_cut && p.n_densities == 0 && (n_cells <= n_cu || 2 * max_lds > lds_max || mixed))
                 T = 512;
             // Cells with generated mechanisms and more nonlinear CVs than 256
             // threads, where each has a CU to itself (by number, or by LDS):
@@ -232,6 +236,14 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
                 pl.max_cells_per_pack = pair;
             } else if (T == 256 && share >= 2) {
                 pl.max_cells_per_pack = share;
+            } else if (T >= 256 && mixed && tasks <= slots * 128) {
+                // as many as leave every CU a workgroup, in 512 threads with
+                // more than 256 branches (us a step, 256 threads filled / by the
+                // mean cell, one or four to a workgroup / so: 846 cells of 20 to
+                // 3000 CVs, a quarter hh, 9.9 / 15.5 / 9.0; 848 of them, soma hh,
+                // 5.5 / 6.8 / 5.4)
+                pl.max_cells_per_pack = (n_cells + n_cu - 1) / n_cu;
+                pl.estimated = T > 256;  // (a state header of its own)
             } else if (T >= 256 && tasks > slots * 128) {
                 pl.max_cells_per_pack = n_cells <= n_cu ? 1 : T;
             } else {

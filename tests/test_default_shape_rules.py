@@ -32,3 +32,38 @@ def test_threads_for_streamed_synapses(branches, n_syn, same, shape):
     d = _cells(1, branches)[0]
     d.syn = [(-1, 0, 2.0, 0.0)] + [(q % branches, 0, 2.0 if same or q % 2 else 3.0, 0.0) for q in range(n_syn - 1)]
     assert _shape([d] * 600) == shape
+
+
+def _mixed(n, big, seed=3):
+    """n cells of 3 to 60 branches and one of `big`."""
+    rng = np.random.default_rng(seed)
+    out = [_cells(1, big, hh_branches=big // 8)[0]]
+    for nb in rng.integers(3, 60, n - 1):
+        out.append(_cells(1, int(nb), hh_branches=int(nb) // 8)[0])
+    return out
+
+
+def test_mixed_cells_share_workgroups():
+    T, _, packs = _shape(_mixed(600, 230))
+    assert T == 256 and 200 <= packs <= 256
+    T, _, packs = _shape(_mixed(200, 230))  # a CU for each
+    assert T == 256 and packs == 200
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,big", [(300, 230), (300, 383)])
+def test_mixed_cells_match_the_oracle(n, big):
+    m = gen.assemble(_mixed(n, big), n_steps=60)
+    ref = oracle.Sim(m)
+    ref.run(60)
+    sim = arbmi.Simulation(m)
+    assert sim.info["block_threads"] >= 256 and sim.info["n_packs"] <= 256
+    sim.step(30)
+    blob = sim.get_state()
+    sim.step(30)
+    V = sim.voltages_host()
+    assert np.max(np.abs(V - ref.state()["V"])) <= 1e-8
+    sim.set_state(blob)
+    sim.step(30)
+    assert np.array_equal(sim.voltages_host(), V)
+    sim.close()
