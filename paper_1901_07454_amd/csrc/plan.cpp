@@ -16,7 +16,7 @@ struct MeanCell {
 };
 
 // LDS of a workgroup of c such cells with at most binary branch points.
-int64_t mean_lds(int len, int64_t c, const MeanCell& m) {
+int64_t mean_lds(int len, int64_t c, const MeanCell& m, bool grads = false) {
     PackDesc D{};
     D.ntk = int32_t(double(c) * m.tasks);
     D.nslot = len * D.ntk;
@@ -24,7 +24,7 @@ int64_t mean_lds(int len, int64_t c, const MeanCell& m) {
     D.nnl = int32_t(double(c) * m.nl);
     D.nsyn = int32_t(double(c) * m.syn);
     D.binary = 1;
-    return pack_lds_bytes(D, 3);
+    return grads ? std::max(pack_lds_bytes(D, 3), reg_adjoint_lds_bytes(D)) : pack_lds_bytes(D, 3);
 }
 
 // Time of a step (us) of n cells, c to a workgroup of T threads whose branches
@@ -267,9 +267,27 @@ Plan choose_plan(const arb_cell* cells, int32_t n_cells, const arb_branch* br, i
             const MeanCell mean{double(all_tasks) / n, double(all_hh) / n, double(all_nl) / n, double(all_syn) / n,
                                 int(max_depth) + 1};
             const bool similar = double(max_tasks) <= 1.25 * mean.tasks + 1 && double(max_nl) <= 1.25 * mean.nl + 8;
+            const int64_t cap = pl.reg_len == 8 ? 2 : 1;  // branches a thread holds
+            // The adjoint kernel gains less from small workgroups than the step
+            // kernel: 256 threads, filled, wherever that leaves two thirds of
+            // the CUs a workgroup (867 cells of 201 hh CVs, forward and gradient,
+            // us a step: a wave for each 39.5, filled 30.4), and for more than 40
+            // branches of up to 16 CVs (98 cells of 820 CVs: 15.8 / 13.3).  Of 250
+            // models 18 were more than 3% slower by the rules above than filled,
+            // and 5 are so.
+            if (grads && similar && pl.block_threads < 256 && max_tasks <= cap * 256) {
+                int64_t fill = 1;
+                while (fill < 256 && (fill + 1) * max_tasks <= cap * 256 &&
+                       mean_lds(pl.reg_len, fill + 1, mean, true) <= pl.lds_budget)
+                    ++fill;
+                if (3 * n_cells >= 2 * n_cu * fill || (pl.reg_len == 16 && max_tasks > 40)) {
+                    pl.block_threads = 256;
+                    pl.reg_slots = pl.wide_slots = int(cap);
+                    pl.max_cells_per_pack = 256;
+                }
+            }
             if (n_cells >= n_cu && max_tasks <= 128 && max_len <= 16 && similar && !grads && p.n_densities == 0 &&
                 24 * max_syn <= kSynLdsMax) {
-                const int64_t cap = pl.reg_len == 8 ? 2 : 1;  // branches a thread holds
                 auto fits = [&](int threads, int64_t c) {
                     return c == 1 || (c * max_tasks <= cap * threads && 24 * c * max_syn <= kSynLdsMax &&
                                       c <= threads && mean_lds(pl.reg_len, c, mean) <= pl.lds_budget);

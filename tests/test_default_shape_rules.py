@@ -67,3 +67,40 @@ def test_mixed_cells_match_the_oracle(n, big):
     sim.step(30)
     assert np.array_equal(sim.voltages_host(), V)
     sim.close()
+
+
+GRADS = {"flags": arbmi.ARB_FLAG_GRADIENTS}
+
+
+@pytest.mark.parametrize("n,branches,n_cv,hh,T", [
+    (800, 25, 8, 25, 256),    # three to 256 threads leave more than two thirds of the CUs one
+    (120, 15, 8, 1, 64),      # they would not
+    (30, 50, 13, 0, 256), (30, 30, 13, 0, 64)])  # more than 40 branches of up to 16 CVs
+def test_threads_for_gradients(n, branches, n_cv, hh, T):
+    assert _shape(_cells(1, branches, n_cv, hh) * n, **GRADS)[0] == T
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,branches,n_cv,hh", [(600, 25, 8, 25), (20, 50, 13, 0)])
+def test_gradients_match_the_oracle(n, branches, n_cv, hh):
+    """Every cell's trace and gradient as the oracle's for one cell: 1e-8 mV
+    and 1e-7 relative, the bounds of the other layouts' tests."""
+    import torch
+
+    from tests.test_gpu_adjoint import model_theta
+    steps = 120
+    one = gen.assemble(_cells(1, branches, n_cv, hh), n_steps=steps)
+    m = gen.assemble(_cells(1, branches, n_cv, hh) * n, n_steps=steps)
+    sim = arbmi.Simulation(m, **GRADS)
+    assert sim.info["block_threads"] == 256 and sim.info["coef_mode"] == 3
+    trace = torch.empty(n, steps, dtype=torch.float64, device="cuda")
+    arbmi.arb_grad_forward(sim.h, steps, 50, trace)
+    dl = np.cos(0.05 * np.arange(steps))[None, :] / steps
+    out = torch.empty(n * model_theta(one).size, dtype=torch.float64, device="cuda")
+    arbmi.arb_grad_backward(sim.h, torch.as_tensor(np.repeat(dl, n, axis=0), device="cuda"), out)
+    tr, g = trace.cpu().numpy(), out.cpu().numpy().reshape(n, -1, 3)
+    sim.close()
+    otr, og = oracle.Sim(one).adjoint(steps, dl)
+    assert np.max(np.abs(tr - otr)) <= 1e-8
+    den = np.maximum(np.abs(og), 1e-3 * np.max(np.abs(og), axis=0, keepdims=True))
+    assert (np.abs(g - og.reshape(1, -1, 3)) <= 1e-7 * den.reshape(1, -1, 3)).all()  # (no passive region: 0 <= 0)
