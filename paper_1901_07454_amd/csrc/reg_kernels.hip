@@ -169,19 +169,22 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
         }
     }
     for (int i = tid; i < pk.nnl; i += T) {
-        NlDesc d = a.nl[pk.nl0 + i];
+        const NlDesc d = a.nl[pk.nl0 + i];
+        NlDesc e = d;
+        if constexpr (M) {
+            // with currents in LDS an entry's first instance and their number
+            // ride in the high halves of its slot and hh instance (LDS holds
+            // fewer than 2^15 of any of them)
+            if (pk.ngen) {
+                const int q0 = a.gen_off[pk.nl0 + i];
+                e.slot |= (q0 - a.gen_pk[p]) << 16;
+                e.hh = (d.hh & 0xffff) | (a.gen_off[pk.nl0 + i + 1] - q0) << 16;
+            }
+        }
+        s_nl[i] = e;
         if (!hh_hbm) s_nlb[i] = a.beta[pk.slot0 + d.slot];
         if (d.hh >= 0) s_hhs[d.hh] = vix(d.slot);
         if (sums) s_sum[i] = a.syn_sum[pk.sum0 + i];
-        // with currents in LDS an entry's first instance and their number ride
-        // in the high halves of its slot and hh instance (LDS holds fewer than
-        // 2^15 of any of them)
-        if (M && pk.ngen) {
-            const int q0 = a.gen_off[pk.nl0 + i];
-            d.slot |= (q0 - a.gen_pk[p]) << 16;
-            d.hh = (d.hh & 0xffff) | (a.gen_off[pk.nl0 + i + 1] - q0) << 16;
-        }
-        s_nl[i] = d;
     }
     if (!pk.binary)
         for (int i = tid; i < pk.nch; i += T) s_ch[i] = a.ch_task[pk.ch0 + i];
