@@ -532,7 +532,8 @@ def main():
     # synapses held in HBM that share reversal potential and decay: a step works
     # on one conductance sum per CV with synapses (at most every CV)
     summed = (24 * info["n_syn"] > 16384 * info["n_cells"]
-              and len(np.unique(m["syn_tau"])) == len(np.unique(m["syn_e"])) == 1)
+              and len(np.unique(m["syn_tau"])) == len(np.unique(m["syn_e"])) == 1
+              and np.exp(-m["dt"] / m["syn_tau"][0]) >= 0.35)
     n_syn_work = min(info["n_syn"], n_cv) if summed else info["n_syn"]
     flops_per_step = FLOPS_PER_CV * n_cv + FLOPS_PER_HH * info["n_hh"] + FLOPS_PER_SYN * n_syn_work
     gen_instances = {}

@@ -212,9 +212,9 @@ typedef struct {
     int32_t reg_slots;        /* branches per thread held in registers; 0 if none are */
     int32_t reg_len;          /* CVs per branch held in registers; 0 if none are */
     int32_t syn_hbm;          /* coef_mode 3: 1 if some workgroup keeps state in HBM: its synapse
-                                 state (too many synapses for LDS; streamed every step, or once
-                                 a launch where the synapses share reversal potential and
-                                 decay), or its hh conductances (a cell too large for LDS
+                                 state (too many synapses for LDS; streamed every step, or
+                                 touched by events only where the synapses share reversal
+                                 potential and decay), or its hh conductances (a cell too large for LDS
                                  otherwise); else 0 */
     int32_t n_classes;        /* launches per step kernel call: classes of workgroups that need
                                  different kernel variants or LDS, run concurrently (0 in

@@ -63,14 +63,17 @@ struct GenStates {
 // 16 CVs in all, one otherwise.  G: some pack of the launch keeps state in
 // HBM, its synapses' or its hh conductances' (without it, those paths are
 // compiled out).  SUM (with G): some pack carries conductance sums (both
-// ways for synapse state in one kernel cost the others 5 to 7% of a step).  REC: the
-// sim is built for gradients; the steps record their states when a.rec_V
+// ways for synapse state in one kernel cost the others 5 to 7% of a step).
+// REC: the sim is built for gradients; the steps record their states when a.rec_V
 // is set (the adjoint's recompute), and the gradient forward runs the same
 // code with it unset, so both produce the same trajectory bit for bit (one
 // wave per SIMD fewer than the plain variant: the recording's addresses take
 // the registers).  M: the model has generated density mechanisms (their
 // currents join the nonlinear CVs' right-hand sides, their states advance
-// with the gates; parameters and states stay in HBM).
+// with the gates; parameters and states stay in HBM; one wave per SIMD fewer
+// too, for the pair of instances in flight: held to three it spills 70
+// registers, 4096 cells of 1017 CVs 153 us a step, 76 with two).  512 threads:
+// two.
 template <int T, int S, int L, bool G, bool REC, bool M = false, bool SUM = false>
 __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ? 2 : 1) : ((S * L <= 8) ? 3 : (S * L <= 16 ? 2 : 1)))
     reg_step_kernel(StepArgs a) {
@@ -135,9 +138,11 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
     const double* g_gna = pk.nhh ? a.hh_gna + pk.hh0 : a.beta + pk.slot0;
     const double* g_gk = pk.nhh ? a.hh_gk + pk.hh0 : a.beta + pk.slot0;
     const bool rec = REC && a.rec_V != nullptr;
-    // a thread's hh CVs two at a time: in 512 threads, which hold large cells;
-    // in 256 it loses (us a step one at a time / two: 256 cells of 321 hh CVs
-    // 4.2 / 4.8, 1024 of 505 9.5 / 11.0, 4096 uneven cells 54.8 / 56.6)
+    // a thread's hh CVs two at a time: in 512 threads, for the large cells of
+    // many hh CVs that the shape is for (us a step one at a time / two: 512
+    // uneven cells of up to 5000 CVs 12.2 / 11.6; 64 cells of 260 branches, 3000
+    // synapses and an hh soma, 4.0 / 4.3); in 256 it loses (256 cells of 321 hh
+    // CVs 4.2 / 4.8, 1024 of 505 9.5 / 11.0, 4096 uneven cells 54.8 / 56.6)
     constexpr bool PAIRS = !REC && !M && T == 512;
     for (int i = tid; i < ns; i += T) {
         const double v = a.V[pk.slot0 + i];
@@ -486,8 +491,7 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
         };
         if constexpr (PAIRS) {
             // every level of an entry's dependent loads (entry, then V and
-            // gates) waited for once for two entries: 1,170 cycles an entry
-            // alone, 980 so (1460 hh CVs in 256 threads)
+            // gates) is waited for once for two entries
             int j = tid;
             for (; j < pk.nnl; j += 2 * T) {
                 const bool two = j + T < pk.nnl;
@@ -633,8 +637,7 @@ __global__ void __launch_bounds__(T, T == 512 ? 2 : (REC || M) ? ((S * L <= 8) ?
             int q0 = tid;
             if constexpr (PAIRS) {
                 // two instances at once: each is a chain of exponentials and
-                // divisions that leaves its SIMD waiting (2,570 cycles alone,
-                // 2,100 each so; 567 instances, 256 threads)
+                // divisions that leaves its SIMD waiting
                 for (; q0 + T < pk.nhh; q0 += 2 * T) {
                     const int q1 = q0 + T;
                     const double v0 = sV[s_hhs[q0]], v1 = sV[s_hhs[q1]];
